@@ -24,7 +24,7 @@ if ROOT not in sys.path:
 
 METRIC = "atom-steps/s LJ cell-list FP32 + % FP32 peak; batched & adjoint vs plain"
 FP32_VECTOR_PEAK_TFLOPS = 157.3  # MI355X: 256 CUs x 2.4 GHz x 256 FP32 flop/clk
-FP32_MATRIX_PEAK_TFLOPS = 157.3  # MI355X dense FP32 matrix-core peak
+F16_MATRIX_PEAK_TFLOPS = 2516.6  # MI355X dense 16-bit matrix-core peak: 16 x the FP32 one
 FLOP_PER_CANDIDATE = 8           # displacement (3) + r^2 (5)
 FLOP_PER_ACCEPTED = 17           # rsqrt, powers, shifted magnitude, 3 accumulating FMAs
 # Hessian-vector product pass of the adjoint, per accepted pair: powers and
@@ -32,7 +32,7 @@ FLOP_PER_ACCEPTED = 17           # rsqrt, powers, shifted magnitude, 3 accumulat
 # d.(w_i - w_j) (5), B times it (1), J accumulation (12), force for d/d eps (6),
 # d.w_i and the sigma term (7)
 FLOP_PER_ACCEPTED_HVP = 59
-MFMA_MIN_HOME, MFMA_MAX_HOME = 11, 16  # home-atom chunks screened on the matrix cores
+MFMA_MIN_HOME, MFMA_MAX_HOME = 11, 32  # home-atom chunks screened on the matrix cores
 
 
 def parse():
@@ -442,7 +442,7 @@ def pair_list_leg(torch, nsteps=100, warm=20, atom_lists=False):
 def pair_counts(sys_, torch, chunk=64):
     """Candidate pairs the 27-cell method tests on the current state, split
     into those screened on the VALU and those screened on the matrix cores
-    (home-atom chunks of 11..16 atoms: a cell's atoms in chunks of `chunk`,
+    (home-atom chunks of 11..32 atoms: a cell's atoms in chunks of `chunk`,
     each chunk against the whole neighbourhood; the kernels take chunks of
     64), and the accepted ordered pairs."""
     import numpy as np
@@ -457,11 +457,8 @@ def pair_counts(sys_, torch, chunk=64):
             for dx in (-1, 0, 1):
                 hood += np.roll(grid, shift=(dz, dy, dx), axis=(0, 1, 2))
     candidates = int((grid * hood).sum())
-    full = grid // chunk  # full chunks: on the matrix cores if 16 atoms, else (64) the VALU
-    last = grid % chunk    # the last chunk
+    last = grid % chunk  # the last chunk (full ones are screened on the VALU)
     mfma_home = np.where((last >= MFMA_MIN_HOME) & (last <= MFMA_MAX_HOME), last, 0)
-    if chunk == MFMA_MAX_HOME:
-        mfma_home = mfma_home + chunk * full
     mfma = int((mfma_home * hood).sum())
     counts, _ = sys_.neighbors(max_per_atom=1)  # counts only; rows truncate (flag cleared below)
     accepted = int(counts.sum().item())
@@ -474,8 +471,8 @@ def alu_roofline(pc, per_accepted, kernel_us):
     """Algorithmic flops of one cell-pair launch split by the unit that runs
     them: the VALU takes the screen of VALU-screened candidates (8 each) and
     every accepted pair's interaction; the matrix cores take the screen of the
-    other candidates (8 each, as dot products). Each part over the launch's
-    duration against its own FP32 peak."""
+    other candidates (8 each, as 16-bit dot products). Each part over the
+    launch's duration against its own unit's peak."""
     t = kernel_us * 1e-6
     vec = FLOP_PER_CANDIDATE * pc["valu_candidates"] + per_accepted * pc["accepted_pairs"]
     mat = FLOP_PER_CANDIDATE * pc["mfma_candidates"]
@@ -489,8 +486,8 @@ def alu_roofline(pc, per_accepted, kernel_us):
         "frac": vec_tf / FP32_VECTOR_PEAK_TFLOPS,
         "kernel_us": kernel_us,
         "vector_flops_per_launch": vec,
-        "matrix": {"achieved": mat_tf, "peak": FP32_MATRIX_PEAK_TFLOPS, "unit": "TFLOP/s",
-                   "frac": mat_tf / FP32_MATRIX_PEAK_TFLOPS, "flops_per_launch": mat},
+        "matrix": {"achieved": mat_tf, "peak": F16_MATRIX_PEAK_TFLOPS, "unit": "TFLOP/s",
+                   "frac": mat_tf / F16_MATRIX_PEAK_TFLOPS, "flops_per_launch": mat},
         "all_flops_tflops": (vec + mat) / t / 1e12,
         **pc,
         # the interaction-only count: the candidate test and interaction of the

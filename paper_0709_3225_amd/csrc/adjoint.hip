@@ -52,12 +52,17 @@ struct AdjOp {
     uint32_t wdelta;    // LDS distance from the position tile to the adjoint-vector tile
     float xi, yi, zi, wx, wy, wz;
     float jx = 0.f, jy = 0.f, jz = 0.f, fx = 0.f, fy = 0.f, fz = 0.f, sg = 0.f;
-    __device__ __forceinline__ void operator()(uint32_t addr, bool live) {
-        const float4 q = lds_load(addr);
-        const float4 wj = lds_load(addr + wdelta);
+    struct Entry {
+        float4 q, w;
+    };
+    __device__ __forceinline__ Entry load(uint32_t addr) const { return Entry{lds_load(addr), lds_load(addr + wdelta)}; }
+    __device__ __forceinline__ void operator()(const Entry& e) {
+        const float4 q = e.q, wj = e.w;
+        keep(q.w);
+        keep(wj.w);
         const float dx = xi - q.x, dy = yi - q.y, dz = zi - q.z;
         const float r2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
-        const bool ok = live && (r2 < k.rc2);
+        const bool ok = r2 < k.rc2;
         const float rinv = __builtin_amdgcn_rsqf(r2);
         const float ir2 = rinv * rinv;
         const float ir6 = ir2 * ir2 * ir2;
@@ -88,11 +93,13 @@ struct VGradOp {
     const PairConsts& k;
     float xi, yi, zi;
     float gx = 0.f, gy = 0.f, gz = 0.f, wsum = 0.f, wsig = 0.f;
-    __device__ __forceinline__ void operator()(uint32_t addr, bool live) {
-        const float4 q = lds_load(addr);
+    using Entry = float4;
+    __device__ __forceinline__ Entry load(uint32_t addr) const { return lds_load(addr); }
+    __device__ __forceinline__ void operator()(const Entry& q) {
+        keep(q.w);
         const float dx = xi - q.x, dy = yi - q.y, dz = zi - q.z;
         const float r2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
-        const bool ok = live && (r2 < k.rc2);
+        const bool ok = r2 < k.rc2;
         const float rinv = __builtin_amdgcn_rsqf(r2);
         const float ir2 = rinv * rinv;
         const float ir6 = ir2 * ir2 * ir2;
@@ -111,11 +118,9 @@ struct VGradOp {
 };
 
 // One pass over the pairs of every home cell: the Hessian-vector product
-// (ADJ) or the virial gradient (VGRAD). Staging as in the force kernel: a
-// neighbourhood that fits one tile is staged in one pass from the row table
-// (cells away from the x faces) or the row-piece table (cells on an x face),
-// with the adjoint vector (ADJ) in a second tile at the same indices; other
-// cells take the LDS segment table and stage in the pass loop. The slice
+// (ADJ) or the virial gradient (VGRAD). Staging and screen as in the force
+// kernel, with the adjoint vector (ADJ) in a second tile at the same indices.
+// The slice
 // reduction reuses the tiles. With nw = blockDim / 64 <= MW wavefronts per
 // cell, wavefront 0 stages, each screens and walks its own contiguous range
 // of every pass's candidates, and wavefront 0 adds the partials (wavefronts
@@ -141,33 +146,15 @@ __global__ void __launch_bounds__(MW * kWave)
     const PairConsts kc = pair_consts(a);
     float ox, oy, oz;
     RowHood rh;
-    const bool interior = row_hood(a, c, rh);  // uniform
-    bool rows = interior && rh.pos[9] <= a.tile_cap && rh.n_home <= kWave;
-    int total, home_first, n_home, home_pos;
+    row_hood(a, c, rh);
+    const bool rows = rh.total <= a.tile_cap && rh.n_home <= kWave;  // uniform
+    int total = rh.total, home_first = rh.home_first, n_home = rh.n_home, home_pos = rh.home_pos;
+    ox = rh.ox;
+    oy = rh.oy;
+    oz = rh.oz;
     if (rows) {
-        ox = rh.ox;
-        oy = rh.oy;
-        oz = rh.oz;
-        total = rh.pos[9];
-        home_first = rh.home_first;
-        n_home = rh.n_home;
-        home_pos = rh.home_pos;
-        if (wv == 0) stage_rows<ADJ ? SECOND_VEC : SECOND_NONE>(a, rh, tile, wtile, wvec);
-    }
-    RowPieces rp;
-    if (!interior) row_pieces(a, c, rp);
-    if (!interior && rp.total <= a.tile_cap && rp.n_home <= kWave) {
-        rows = true;
-        ox = rp.ox;
-        oy = rp.oy;
-        oz = rp.oz;
-        total = rp.total;
-        home_first = rp.home_first;
-        n_home = rp.n_home;
-        home_pos = rp.home_pos;
-        if (wv == 0) stage_pieces<ADJ ? SECOND_VEC : SECOND_NONE>(a, rp, tile, wtile, wvec);
-    }
-    if (!rows) {
+        if (wv == 0) stage_hood<ADJ ? SECOND_VEC : SECOND_NONE>(a, rh, tile, wtile, wvec);
+    } else {
         load_neighbourhood(a, c, nb, ox, oy, oz);
         total = nb.total;
         home_first = nb.home_first;
@@ -180,24 +167,15 @@ __global__ void __launch_bounds__(MW * kWave)
     double acc0 = 0.0, acc1 = 0.0;
     for (int h0 = 0; h0 < n_home; h0 += kWave) {
         const int nh = min(kWave, n_home - h0);
-        // 11..16 home atoms: matrix-core screen with four slices, lane =
-        // (atom lane % 16, slice lane / 16), as in the force kernel
-        const bool mf = nh >= kMfmaMinHome && nh <= 16;  // uniform
-        const int ns = mf ? 4 : min(kMaxSlices, kWave / nh);
-        const int hstride = mf ? 16 : nh;
-        const int h = lane % hstride, s = lane / hstride;
-        const bool act = mf ? h < nh : s < ns;
+        const HomeLanes hl = home_lanes(nh);
+        const int ns = hl.ns, hstride = hl.hs, h = hl.h, s = hl.s;
+        const bool act = hl.act;
         float4 pi = make_float4(0.f, 0.f, 0.f, 0.f), wi = pi;
         if (act) {
             pi = a.pos0[home_first + h0 + h];
             if (ADJ) wi = wvec[home_first + h0 + h];
         }
         const float xi = pi.x - ox, yi = pi.y - oy, zi = pi.z - oz;
-        const float ai = fmaf(zi, zi, fmaf(yi, yi, xi * xi));
-        const float thr_i = act ? a.screen2 - ai : -__builtin_huge_valf();
-        const float mx = -2.0f * xi, my = -2.0f * yi, mz = -2.0f * zi;
-        const float bval = s == 3 ? 1.0f : (act ? (s == 0 ? mx : (s == 1 ? my : mz)) : 0.0f);
-        const float cneg = -thr_i;
         float v0 = 0.f, v1 = 0.f, v2 = 0.f, v3 = 0.f, v4 = 0.f, v5 = 0.f, v6 = 0.f;
         for (int t0 = 0; t0 < total; t0 += a.tile_cap) {
             const int tn = min(a.tile_cap, total - t0);
@@ -207,47 +185,28 @@ __global__ void __launch_bounds__(MW * kWave)
             }
             if (wv == 0) {
                 for (int t = lane; t < kTilePad; t += kWave) {
-                    tile[tn + t] = make_float4(0.f, 0.f, 0.f, __builtin_huge_valf());
+                    tile[tn + t] = pad_entry(a);
                     if (ADJ) wtile[tn + t] = make_float4(0.f, 0.f, 0.f, 0.f);
                 }
             }
             __syncthreads();
             const int self_t = home_pos + h0 + h - t0;
-            // spans: 128 candidates per lane (32 blocks of 16 with the matrix cores);
-            // this wavefront's groups [g_lo, g_hi), split at multiples of the
-            // screen's step (four blocks, or four VALU groups)
-            const int groups_all = mf ? 4 * ((tn + 15) / 16) : (tn + ns - 1) / ns;
-            const int unit = mf ? 16 : kScreenUnroll;
-            const int nu = (groups_all + unit - 1) / unit;
-            const int g_lo = unit * ((nu * wv) / nw), g_hi = min(groups_all, unit * ((nu * (wv + 1)) / nw));
-            for (int g0 = g_lo; g0 < g_hi; g0 += kGroups) {
-                const int groups = min(kGroups, g_hi - g0);
-                const int first = mf ? 4 * g0 + s : g0 * ns + (act ? s : 0);
-                uint32_t wd[kWords];
-                if (mf) {
-                    screen_mfma(tile, 4 * g0, groups / 4, bval, cneg, wd);
-                } else {
-                    switch (ns) {
-                        case 2: screen_span<2>(tile, first, ns, groups, mx, my, mz, thr_i, wd); break;
-                        case 3: screen_span<3>(tile, first, ns, groups, mx, my, mz, thr_i, wd); break;
-                        case 5: screen_span<5>(tile, first, ns, groups, mx, my, mz, thr_i, wd); break;
-                        case 6: screen_span<6>(tile, first, ns, groups, mx, my, mz, thr_i, wd); break;
-                        default: screen_span<0>(tile, first, ns, groups, mx, my, mz, thr_i, wd); break;
-                    }
-                }
-                if (act) clear_self(self_t, first, ns, groups, wd);
-                if (ADJ) {
+            const uint32_t pad = lds_address(tile + tn);
+            for_each_words<false>(a, tile, tn, hl, nh, xi, yi, zi, a.screen2, a.screen16, self_t, wv, nw,
+                           [](uint32_t (&)[kWords], int) { return false; },
+                           [&](uint32_t (&wd)[kWords], int first, int, bool) {
+                if constexpr (ADJ) {
                     AdjOp op{kc, lds_address(wtile) - lds_address(tile), xi, yi, zi, wi.x, wi.y, wi.z};
                     op.jx = v0; op.jy = v1; op.jz = v2; op.fx = v3; op.fy = v4; op.fz = v5; op.sg = v6;
-                    walk_bits(ns, lds_address(tile + first), wd[0], wd[1], wd[2], wd[3], op);
+                    walk_bits(ns, lds_address(tile + first), pad, wd, op);
                     v0 = op.jx; v1 = op.jy; v2 = op.jz; v3 = op.fx; v4 = op.fy; v5 = op.fz; v6 = op.sg;
                 } else {
                     VGradOp op{kc, xi, yi, zi};
                     op.gx = v0; op.gy = v1; op.gz = v2; op.wsum = v3; op.wsig = v4;
-                    walk_bits(ns, lds_address(tile + first), wd[0], wd[1], wd[2], wd[3], op);
+                    walk_bits(ns, lds_address(tile + first), pad, wd, op);
                     v0 = op.gx; v1 = op.gy; v2 = op.gz; v3 = op.wsum; v4 = op.wsig;
                 }
-            }
+            });
         }
         // partials of each home atom, summed over wavefronts in order and
         // slices in order (red aliases the tiles: every lane has finished its

@@ -4,6 +4,8 @@
 // accepted bits. See forces.hip for the design.
 #pragma once
 
+#include <type_traits>
+
 #include "md_device.h"
 
 namespace mdlj {
@@ -320,68 +322,111 @@ __device__ __forceinline__ void stage_whole(const SimArgs& a, const HoodSegs& h,
     }
 }
 
-// Neighbourhood of a home cell away from the x faces (1 <= ix <= nc - 2), held
-// in scalar registers: its nine x-rows (dy, dz) of three cells each are
-// contiguous in the sorted arrays and need no image shift in x, so the row
-// bounds come from nine uniform loads of four CSR offsets each and the
-// staging below needs no per-segment table lookups.
-struct RowHood {
-    int first[9];  // sorted slot of each row's first atom
-    int pos[10];   // neighbourhood index of each row's first atom; pos[9] = total
-    int home_first, n_home, home_pos;
-    float ox, oy, oz;  // home-cell origin
-    float fy[3], fz[3];  // frame offsets o - sh of the rows with dy, dz = -1, 0, 1
+// Neighbourhood of a home cell for the one-pass staging, in scalar registers:
+// nine x-rows (dy, dz). In each row the cells that need no image shift in x are
+// consecutive in the sorted arrays (piece A: three cells, or two for a home
+// cell on an x face); on an x face the row's third cell wraps around the box
+// (piece B, one cell, shifted by -+L in x). Pieces are staged in the order
+// A0..A8, B0..B8, so the tile holds the neighbourhood without gaps. The CSR
+// offsets come from scalar loads (the table is uniform, and the vector units
+// are what bounds the cell passes: one vector load with its offsets moved to
+// scalar registers lane by lane took about 60 vector instructions more per
+// cell).
+struct Pieces {
+    int first[9];  // sorted slot of each piece's first atom
+    int pos[10];   // tile index of each piece's first atom; pos[9]: of the one after the last
 };
 
-// Fill r for home cell c (local index, uniform); false for a cell on an x
-// face. Lane k < 9 loads the CSR offsets of row k's cells ix - 1 .. ix + 2
-// (one 16-byte load, one round trip for the table); the values then move to
-// scalar registers.
-typedef int Int4u __attribute__((ext_vector_type(4), aligned(4)));
+struct RowHood {
+    Pieces a;
+    int total, home_first, n_home, home_pos;
+    int ix, iy, iz;
+    float ox, oy, oz;    // home-cell origin
+    float fxb;           // frame offset in x of the B pieces
+    float fy[3], fz[3];  // frame offsets o - sh of the rows with dy, dz = -1, 0, 1
+    bool face;
+};
 
-__device__ __forceinline__ bool row_hood(const SimArgs& a, int c, RowHood& r) {
-#pragma clang fp contract(off)
-    const int lane = __lane_id();
+__device__ __forceinline__ int scalar_load(const int* p) {
+    return *(const __attribute__((address_space(4))) int*)(reinterpret_cast<uintptr_t>(p));
+}
+
+// c / nc and c % nc for a cell or row index 0 <= c < nc^3 (uniform): the
+// quotient from nc_magic = ceil(2^32 / nc) is at most one too large.
+__device__ __forceinline__ int div_nc(const SimArgs& a, int c, int& rem) {
+    int q = static_cast<int>(__umulhi(static_cast<uint32_t>(c), a.nc_magic));
+    rem = c - q * a.nc;
+    if (rem < 0) {
+        --q;
+        rem += a.nc;
+    }
+    return q;
+}
+
+// CSR offsets of cells [c0, c0 + n) of the nine x-rows around (iy, iz): the
+// first atom of each row's piece and the one past its last.
+__device__ __forceinline__ void piece_bounds(const SimArgs& a, const RowHood& r, int c0, int n, int (&first)[9],
+                                             int (&end)[9]) {
     const int nc = a.nc;
-    const int ix = __builtin_amdgcn_readfirstlane(c % nc);
-    const int iy = __builtin_amdgcn_readfirstlane((c / nc) % nc);
-    const int iz = __builtin_amdgcn_readfirstlane(c / (nc * nc));
-    if (ix < 1 || ix > nc - 2) return false;
-    r.ox = static_cast<float>(ix) * a.s;
-    r.oy = static_cast<float>(iy) * a.s;
-    r.oz = static_cast<float>(iz) * a.s;
-    r.fy[0] = iy == 0 ? r.oy + a.box : r.oy;
+    const int* base = a.start + a.cbase + c0;
+    // (negative below the edge: the sign bit selects, in scalar instructions)
+    const int by = r.iy - 1, bz = r.iz - 1, ey = r.iy + 1 - nc, ez = r.iz + 1 - nc;
+    const int jy[3] = {by + (by >> 31 & nc), r.iy, ey + (ey >> 31 & nc)};
+    const int jz[3] = {bz + (bz >> 31 & nc), r.iz, ez + (ez >> 31 & nc)};
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+        const int* p = base + nc * (jy[k % 3] + nc * jz[k / 3]);
+        first[k] = scalar_load(p);
+        end[k] = scalar_load(p + n);
+    }
+}
+
+// Tile indices of nine pieces from p on; returns the one after the last.
+__device__ __forceinline__ int place_pieces(Pieces& t, const int (&end)[9], int p) {
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+        t.pos[k] = p;
+        p += end[k] - t.first[k];
+    }
+    t.pos[9] = p;
+    return p;
+}
+
+__device__ __forceinline__ void row_hood(const SimArgs& a, int c_in, RowHood& r) {
+#pragma clang fp contract(off)
+    const int c = __builtin_amdgcn_readfirstlane(c_in);
+    const int nc = a.nc;
+    const int row = div_nc(a, c, r.ix);
+    r.iz = div_nc(a, row, r.iy);
+    r.face = r.ix == 0 || r.ix == nc - 1;
+    // piece A: three cells, or two on a face
+    const int a0 = r.ix == 0 ? 0 : r.ix - 1, n = r.face ? 2 : 3;
+    int end[9];
+    piece_bounds(a, r, a0, n, r.a.first, end);
+    const int* home = a.start + a.cbase + c;
+    r.home_first = scalar_load(home);
+    r.n_home = scalar_load(home + 1) - r.home_first;
+    const int by = r.iy - 1, bz = r.iz - 1, ey = r.iy + 1 - nc, ez = r.iz + 1 - nc;
+    r.ox = static_cast<float>(r.ix) * a.s;
+    r.oy = static_cast<float>(r.iy) * a.s;
+    r.oz = static_cast<float>(r.iz) * a.s;
+    // (the shifts are selected as scalars; adding zero is exact)
+    const int L = __float_as_int(a.box);
+    r.fxb = r.ox + __int_as_float(r.ix == 0 ? L : L ^ static_cast<int>(0x80000000u));
+    r.fy[0] = r.oy + __int_as_float(by >> 31 & L);
     r.fy[1] = r.oy;
-    r.fy[2] = iy == nc - 1 ? r.oy - a.box : r.oy;
-    r.fz[0] = iz == 0 ? r.oz + a.box : r.oz;
+    r.fy[2] = r.oy - __int_as_float(~(ey >> 31) & L);
+    r.fz[0] = r.oz + __int_as_float(bz >> 31 & L);
     r.fz[1] = r.oz;
-    r.fz[2] = iz == nc - 1 ? r.oz - a.box : r.oz;
-    Int4u row = {0, 0, 0, 0};
-    if (lane < 9) {
-        int jy = iy + lane % 3 - 1, jz = iz + lane / 3 - 1;
-        jy = jy < 0 ? jy + nc : (jy >= nc ? jy - nc : jy);
-        jz = jz < 0 ? jz + nc : (jz >= nc ? jz - nc : jz);
-        row = *reinterpret_cast<const Int4u*>(a.start + a.cbase + (ix - 1) + nc * (jy + nc * jz));
-    }
-    int s0[9], s3[9];
+    r.fz[2] = r.oz - __int_as_float(~(ez >> 31) & L);
+    r.total = place_pieces(r.a, end, 0);
+    r.home_pos = r.a.pos[4] + (r.home_first - r.a.first[4]);
+    if (r.face) {
+        int f[9], e[9];
+        piece_bounds(a, r, r.ix == 0 ? nc - 1 : 0, 1, f, e);
 #pragma unroll
-    for (int k = 0; k < 9; ++k) {
-        s0[k] = __builtin_amdgcn_readlane(row.x, k);
-        s3[k] = __builtin_amdgcn_readlane(row.w, k);
+        for (int k = 0; k < 9; ++k) r.total += e[k] - f[k];
     }
-    const int s1 = __builtin_amdgcn_readlane(row.y, 4), s2 = __builtin_amdgcn_readlane(row.z, 4);
-    int p = 0;
-#pragma unroll
-    for (int k = 0; k < 9; ++k) {
-        r.first[k] = s0[k];
-        r.pos[k] = p;
-        if (k == 4) r.home_pos = p + (s1 - s0[k]);
-        p += s3[k] - s0[k];
-    }
-    r.home_first = s1;
-    r.n_home = s2 - s1;
-    r.pos[9] = p;
-    return true;
 }
 
 // Second tile of the staging functions below (SECOND): none; the untranslated
@@ -404,59 +449,81 @@ __device__ __forceinline__ uint32_t list_entry(int slot, int sx, int sy, int sz)
     return static_cast<uint32_t>(slot) | (static_cast<uint32_t>((sx + 1) + 3 * (sy + 1) + 9 * (sz + 1)) << kSlotBits);
 }
 
-// Staging of a RowHood neighbourhood in one pass (total <= tile capacity), by
-// the same unmasked scheme as stage_whole (rows tile [0, total) in order).
-template <int SECOND = SECOND_NONE>
-__device__ __forceinline__ void stage_rows(const SimArgs& a, const RowHood& r, float4* tile, float4* raw = nullptr,
-                                           const float4* vsrc = nullptr) {
-    const int lane = __lane_id();
-    const int last = a.natoms - 1;
-    const char* pbase = reinterpret_cast<const char*>(a.pos0);
-    const char* vbase = reinterpret_cast<const char*>(vsrc);
+// The float4 at byte offset off of an array, by a bounds-checked buffer load
+// (offsets past the end give zeros): no 64-bit address arithmetic, and no
+// clamps. W: with the fourth component.
+template <bool W>
+__device__ __forceinline__ float4 load_slot(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+    if (W) {
+        const auto v = __builtin_amdgcn_raw_buffer_load_b128(r, static_cast<int>(off), 0, 0);
+        return make_float4(__uint_as_float(v[0]), __uint_as_float(v[1]), __uint_as_float(v[2]), __uint_as_float(v[3]));
+    }
+    const auto v = __builtin_amdgcn_raw_buffer_load_b96(r, static_cast<int>(off), 0, 0);
+    return make_float4(__uint_as_float(v[0]), __uint_as_float(v[1]), __uint_as_float(v[2]), 0.f);
+}
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t slot_buffer(const float4* p, int n) {
+    // stride 0, n <= 2^27 16-byte slots, 32-bit data format
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float4*>(p), 0, static_cast<int>(static_cast<uint32_t>(n) << 4),
+                                             0x00020000);
+}
+
+// Staging of nine pieces in one pass, with few instructions per piece: every
+// lane loads and stores entry pos + lane of each piece whether or not it has
+// that many atoms. Pieces are written in order and without gaps, so the
+// surplus entries of a piece (up to pos + 63) are overwritten by a later one,
+// or fall into the padding after the total, which the caller fills
+// afterwards. Atoms 64 and up of a longer piece follow, masked, after every
+// piece's first 64: no surplus store reaches that far. The tile needs room for
+// total + 63 entries.
+template <int SECOND>
+__device__ __forceinline__ void stage_nine(const SimArgs& a, const RowHood& r, const Pieces& t, float fx, float4* tile,
+                                           float4* raw, const float4* vsrc) {
+    const int lane = lane_here();
+    const uint32_t lane16 = 16u * static_cast<uint32_t>(lane);
+    const __amdgpu_buffer_rsrc_t pos = slot_buffer(a.pos0, a.natoms);
     float4 q[9];
 #pragma unroll
-    for (int k = 0; k < 9; ++k) {
-        const uint32_t off = static_cast<uint32_t>(min(r.first[k] + lane, last)) << 4;
-        q[k] = *reinterpret_cast<const float4*>(pbase + off);
-    }
+    for (int k = 0; k < 9; ++k) q[k] = load_slot<SECOND == SECOND_RAW>(pos, lane16 + 16u * t.first[k]);
     uint32_t* codes = reinterpret_cast<uint32_t*>(raw);
+    const int sx = SECOND == SECOND_CODE ? image_shift(r.ox, fx, a.box) : 0;
 #pragma unroll
     for (int k = 0; k < 9; ++k) {
-        const float x = q[k].x - r.ox;
+        const float x = q[k].x - fx;
         const float y = q[k].y - r.fy[k % 3];
         const float z = q[k].z - r.fz[k / 3];
-        tile[r.pos[k] + lane] = make_float4(x, y, z, x * x + y * y + z * z);
-        if (SECOND == SECOND_RAW) raw[r.pos[k] + lane] = q[k];
+        tile[t.pos[k] + lane] = make_float4(x, y, z, x * x + y * y + z * z);
+        if (SECOND == SECOND_RAW) raw[t.pos[k] + lane] = q[k];
         if (SECOND == SECOND_CODE)
-            codes[r.pos[k] + lane] = list_entry(r.first[k] + lane, 0, image_shift(r.oy, r.fy[k % 3], a.box),
+            codes[t.pos[k] + lane] = list_entry(t.first[k] + lane, sx, image_shift(r.oy, r.fy[k % 3], a.box),
                                                 image_shift(r.oz, r.fz[k / 3], a.box));
+        // store as each load arrives: nine results held for one burst of
+        // stores would cost 36 more registers
         __builtin_amdgcn_sched_barrier(0);
     }
     if (SECOND == SECOND_VEC) {  // a second round (the positions' registers are free again)
+        const __amdgpu_buffer_rsrc_t vec = slot_buffer(vsrc, a.natoms);
+#pragma unroll
+        for (int k = 0; k < 9; ++k) q[k] = load_slot<true>(vec, lane16 + 16u * t.first[k]);
 #pragma unroll
         for (int k = 0; k < 9; ++k) {
-            const uint32_t off = static_cast<uint32_t>(min(r.first[k] + lane, last)) << 4;
-            q[k] = *reinterpret_cast<const float4*>(vbase + off);
-        }
-#pragma unroll
-        for (int k = 0; k < 9; ++k) {
-            raw[r.pos[k] + lane] = q[k];
+            raw[t.pos[k] + lane] = q[k];
             __builtin_amdgcn_sched_barrier(0);
         }
     }
 #pragma unroll
     for (int k = 0; k < 9; ++k) {
-        const int len = r.pos[k + 1] - r.pos[k];
+        const int len = t.pos[k + 1] - t.pos[k];
         if (len > kWave) {  // uniform; rare
             for (int off = kWave + lane; off - lane < len; off += kWave) {
                 if (off < len) {
-                    const float4 u = a.pos0[r.first[k] + off];
-                    const float x = u.x - r.ox, y = u.y - r.fy[k % 3], z = u.z - r.fz[k / 3];
-                    tile[r.pos[k] + off] = make_float4(x, y, z, x * x + y * y + z * z);
-                    if (SECOND == SECOND_RAW) raw[r.pos[k] + off] = u;
-                    if (SECOND == SECOND_VEC) raw[r.pos[k] + off] = vsrc[r.first[k] + off];
+                    const float4 u = a.pos0[t.first[k] + off];
+                    const float x = u.x - fx, y = u.y - r.fy[k % 3], z = u.z - r.fz[k / 3];
+                    tile[t.pos[k] + off] = make_float4(x, y, z, x * x + y * y + z * z);
+                    if (SECOND == SECOND_RAW) raw[t.pos[k] + off] = u;
+                    if (SECOND == SECOND_VEC) raw[t.pos[k] + off] = vsrc[t.first[k] + off];
                     if (SECOND == SECOND_CODE)
-                        codes[r.pos[k] + off] = list_entry(r.first[k] + off, 0, image_shift(r.oy, r.fy[k % 3], a.box),
+                        codes[t.pos[k] + off] = list_entry(t.first[k] + off, sx, image_shift(r.oy, r.fy[k % 3], a.box),
                                                            image_shift(r.oz, r.fz[k / 3], a.box));
                 }
             }
@@ -464,10 +531,24 @@ __device__ __forceinline__ void stage_rows(const SimArgs& a, const RowHood& r, f
     }
 }
 
+// The whole neighbourhood of r in one pass (total <= tile capacity).
+template <int SECOND = SECOND_NONE>
+__device__ __forceinline__ void stage_hood(const SimArgs& a, const RowHood& r, float4* tile, float4* raw = nullptr,
+                                           const float4* vsrc = nullptr) {
+    stage_nine<SECOND>(a, r, r.a, r.ox, tile, raw, vsrc);
+    if (r.face) {  // the table of the B pieces is read again (two tables do not fit the scalar registers)
+        Pieces b;
+        int end[9];
+        piece_bounds(a, r, r.ix == 0 ? a.nc - 1 : 0, 1, b.first, end);
+        place_pieces(b, end, r.a.pos[9]);
+        stage_nine<SECOND>(a, r, b, r.fxb, tile, raw, vsrc);
+    }
+}
+
 // Stage neighbourhood atoms [t0, t0 + tn) of the table in nb (an interior
 // cell's neighbourhood costs one global round trip).
-// B chunks in flight per batch (default: 9, or 5 with a vector).
-template <bool ID_IN_W, bool WITH_VEC = false, int B = (WITH_VEC ? 5 : 9)>
+// B chunks in flight per batch (default: 9, or 3 with a vector).
+template <bool ID_IN_W, bool WITH_VEC = false, int B = (WITH_VEC ? 3 : 9)>
 __device__ __forceinline__ void stage_tile(const SimArgs& a, const Neighbourhood& nb, float4* tile,
                                            int t0, int tn, const float4* vec = nullptr,
                                            float4* vtile = nullptr) {
@@ -505,16 +586,17 @@ __device__ __forceinline__ void stage_codes(const SimArgs& a, const Neighbourhoo
 }
 
 // Cell-pair kernels. One wavefront per home cell; lane = (home atom h, slice s)
-// with ns = floor(64 / home atoms) slices, so a cell of 15 atoms keeps 60
-// lanes busy. The staged candidates are screened in spans of up to 128 per
-// lane:
-//  screen : lane (h, s) tests candidates s, s + ns, s + 2 ns, ... (slices
-//           interleave, so every slice samples the whole neighbourhood and
-//           the slices of one atom find similar numbers of partners) with
-//           r^2 - |x_i|^2 = |x_j|^2 - 2 x_i.x_j (three FMAs) against a bound a
-//           little above r_c^2, and shifts each verdict's sign bit into a
-//           32-bit accept word (one v_alignbit). Lanes of one slice read the
-//           same candidate, so every LDS read of the screen is a broadcast.
+// with ns slices per atom: four for 11..16 atoms, else floor(64 / atoms) (at
+// most 16), so that a cell of 15 atoms keeps 60 lanes busy and one of 20 atoms
+// too. The staged candidates are screened in spans of up to 128 per lane (256
+// with two slices):
+//  screen : lane (h, s) gets the verdicts on candidates s, s + ns, s + 2 ns, ...
+//           (slices interleave, so every slice samples the whole neighbourhood
+//           and the slices of one atom find similar numbers of partners): the
+//           sign of r^2 - bound = |x_j|^2 - 2 x_i.x_j - (bound - |x_i|^2)
+//           against a bound a little above r_c^2, shifted into 32-bit accept
+//           words. Cells of 11..32 atoms screen on the matrix cores, others on
+//           the VALU.
 //  pairs  : the home atom's own bit is cleared; every lane walks the set bits
 //           of its words, recomputes the exact displacement, keeps
 //           r^2 < r_c^2 and applies the kernel's pair operation (for the force
@@ -522,11 +604,12 @@ __device__ __forceinline__ void stage_codes(const SimArgs& a, const Neighbourhoo
 // Slice partials are summed in slice order, so the result does not depend on
 // timing.
 constexpr int kWords = 4;              // accept words per lane per span
-constexpr int kGroups = 32 * kWords;   // candidates per lane per span
+constexpr int kGroups = 32 * kWords;   // candidates per lane of one walk
 constexpr int kMaxSlices = 16;
 constexpr int kScreenUnroll = 4;
 constexpr int kTilePad = kMaxSlices * (kScreenUnroll + 1);  // far-away entries after the staged atoms
 constexpr int kMaxCellWaves = 4;                            // wavefronts per force workgroup
+constexpr int kMfmaMinHome = 11, kMfmaMaxHome = 32;  // home atoms screened on the matrix cores
 
 // LDS entries (float4) of a force workgroup: the tile and its padding, which
 // the reduction reuses (five floats per lane and wavefront)
@@ -534,7 +617,44 @@ __host__ __device__ constexpr size_t cell_lds_entries(int tile_cap, int waves) {
     return static_cast<size_t>(tile_cap + kTilePad > 80 * waves ? tile_cap + kTilePad : 80 * waves);
 }
 
-// Screen of one span: word w, bit 31 - k holds the verdict on the lane's
+// The lanes of a chunk of nh <= 64 home atoms: lane l holds atom h = l % hs and
+// slice s = l / hs if act.
+struct HomeLanes {
+    int ns, hs;  // uniform
+    int h, s;
+    bool act;
+};
+
+__device__ __forceinline__ HomeLanes home_lanes(int nh) {
+    const int lane = lane_here();
+    HomeLanes v;
+    if (nh >= kMfmaMinHome && nh <= 16) {  // uniform
+        v.ns = 4;
+        v.hs = 16;
+        v.h = lane & 15;
+        v.s = lane >> 4;
+        v.act = v.h < nh;
+    } else {
+        // x / nh for x <= 64, nh <= 64: x ceil(2^16 / nh) / 2^16
+        const uint32_t m = (65535u + nh) / static_cast<uint32_t>(nh);
+        v.ns = min(kMaxSlices, static_cast<int>((64u * m) >> 16));
+        v.hs = nh;
+        v.s = static_cast<int>((static_cast<uint32_t>(lane) * m) >> 16);
+        v.h = lane - v.s * nh;
+        v.act = v.s < v.ns;
+    }
+    return v;
+}
+
+// The padding entries after the staged atoms: 100 cell sides away on every
+// axis, so that no screen and no cutoff test accepts them (r_c is at most a
+// cell side; the scaled values stay finite in 16 bits).
+__device__ __forceinline__ float4 pad_entry(const SimArgs& a) {
+    const float far = 100.0f * a.s;
+    return make_float4(far, far, far, 3.0f * far * far);
+}
+
+// VALU screen of one span: word w, bit 31 - k holds the verdict on the lane's
 // candidate 32 w + k, i.e. tile entry first + (32 w + k) * ns. groups is the
 // largest candidate count of any slice (uniform); entries past the staged
 // atoms are padding that never passes. NS > 0 fixes the stride at compile
@@ -565,6 +685,204 @@ __device__ __forceinline__ void screen_span(const float4* tile, int first, int n
     }
 }
 
+// v of lane src (0 .. 63).
+__device__ __forceinline__ int from_lane(int v, int src) { return __builtin_amdgcn_ds_bpermute(4 * src, v); }
+__device__ __forceinline__ uint32_t from_lane(uint32_t v, int src) {
+    return static_cast<uint32_t>(from_lane(static_cast<int>(v), src));
+}
+__device__ __forceinline__ float from_lane(float v, int src) { return __int_as_float(from_lane(__float_as_int(v), src)); }
+
+// ---- screen on the matrix cores ------------------------------------------
+// The screen runs as matrix products D = A B + C with A 16 candidates (rows),
+// B 16 home atoms (columns) and D[j][i] = r^2 - bound, negative iff accepted.
+// Lane l receives D[4 (l / 16) + q][l % 16], q = 0..3. Row 4 r + q is
+// candidate 4 b + q of slice r for block b, so that lane (atom l % 16, r = l /
+// 16) gets the verdicts on its slice's candidates in order: four sign bits per
+// block, one v_alignbit each. The words are those of the VALU screen, and the
+// same walk takes them.
+//  * Four slices (11..16 atoms): r = 0..3 are the slices.
+//  * Three slices (17..21 atoms): r = 0..2; r = 3 goes unused. The atoms past
+//    16 take a second product, and the words move to the walk's lanes.
+//  * Two slices (22..32 atoms): r % 2 is the slice, r / 2 the half of its
+//    candidates, so that a lane walks two sets of words in turn.
+// The products are 16-bit (16 x 16 x 16): a 32-bit 16 x 16 x 4 product takes
+// 32 cycles in which the SIMD issues no vector instruction (time per wavefront
+// = 4 x vector instructions + product cycles, measured), the 16-bit one runs
+// beside them. In units of the cell side, with v = x_i and u = x_j - 1/2:
+//   r^2 = |x_j|^2 - 2 v.u + (|v|^2 - v.1),
+// so one K quarter (four values) holds (u, |x_j|^2) against (-2 v, 1) and the
+// rest goes to C in 32 bits. Each of A's four lane groups holds the candidates
+// of one of four blocks; a block's product takes them against a B that is zero
+// in the other groups, so a candidate is read from LDS and rounded once. The
+// bound is raised by more than the rounding can take off (screen16_bound on the
+// host), so no pair that the exact test accepts is dropped; the few candidates
+// accepted beyond r_c add exact zeros.
+// Measured against the 32-bit product (11..16 atoms) and the VALU (17..32), with
+// the walk's loads ahead of its arithmetic and the neighbourhood table in scalar
+// registers; same results bit for bit, time of one step's force kernel:
+// N = 2,048,000 (15 atoms a cell) 324 -> 292 us, N = 256,000 53.5 -> 49.9 us (per
+// wavefront 504 matrix cycles for 804, waiting 1,270 cycles for 1,840),
+// N = 4,000 16.1 -> 14.2 us, a gas of 14 a cell 44.0 -> 42.0 us (N = 256,000),
+// 16 a cell and more (VALU before) 32.2 -> 30.1 us (N = 108,000). Up to ten atoms
+// keep six or more slices, whose candidates a product of sixteen columns would
+// serve less than two thirds full: the VALU screen stays there.
+typedef float mfma_f4 __attribute__((ext_vector_type(4)));
+typedef _Float16 half4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ half4 as_half4(uint32_t lo, uint32_t hi) {
+    typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(half4, (u2{lo, hi}));
+}
+
+// A group's operands in this lane: B of each block of four (zero outside the
+// block's lane group) and C.
+struct HomeOps {
+    half4 b[4];
+    float c;
+};
+
+// vx, vy, vz: position of the lane's column's home atom in units of the cell
+// side (on: it has one).
+__device__ __forceinline__ HomeOps home_ops(float vx, float vy, float vz, bool on, float bound16) {
+    const int group = lane_here() >> 4;
+    half4 p = {static_cast<_Float16>(-2.0f * vx), static_cast<_Float16>(-2.0f * vy), static_cast<_Float16>(-2.0f * vz),
+               static_cast<_Float16>(1.0f)};
+    if (!on) p = half4{0, 0, 0, static_cast<_Float16>(1.0f)};
+    typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+    const u2 w = __builtin_bit_cast(u2, p);
+    HomeOps h;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) h.b[k] = as_half4(group == k ? w[0] : 0u, group == k ? w[1] : 0u);
+    h.c = on ? fmaf(vz, vz, fmaf(vy, vy, vx * vx)) - (vx + vy + vz) - bound16 : __builtin_huge_valf();
+    return h;
+}
+
+// Screen nblk <= 32 blocks of four candidates per row group: word w, bit
+// 31 - k holds the verdict on the row group's candidate 32 w + k. base: this
+// lane's candidate of the first four blocks; four blocks on, it lies 16 NS
+// entries further (NS: slices).
+template <int NS>
+__device__ __forceinline__ void screen_mfma(const float4* base, int nblk, float inv_s, const HomeOps& h,
+                                            uint32_t (&wd)[kWords]) {
+    const mfma_f4 c = {h.c, h.c, h.c, h.c};
+    const float inv_s2 = inv_s * inv_s;
+    auto four = [&](int g, uint32_t& bits) {
+        const float4 x = base[g * 16 * NS];
+        // scaled and rounded, two values per register (in one block, with the
+        // two wait states that a product needs after its operands' writes)
+        uint32_t lo, hi;
+        asm("v_fma_mixlo_f16 %0, %2, %6, -0.5 op_sel_hi:[0,0,0]\n\t"
+            "v_fma_mixlo_f16 %1, %4, %6, -0.5 op_sel_hi:[0,0,0]\n\t"
+            "v_fma_mixhi_f16 %0, %3, %6, -0.5 op_sel_hi:[0,0,0]\n\t"
+            "v_fma_mixhi_f16 %1, %5, %7, 0 op_sel_hi:[0,0,0]\n\t"
+            "s_nop 1"
+            : "=&v"(lo), "=&v"(hi)
+            : "v"(x.x), "v"(x.y), "v"(x.z), "v"(x.w), "s"(inv_s), "s"(inv_s2));
+        const half4 a = as_half4(lo, hi);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const mfma_f4 d = __builtin_amdgcn_mfma_f32_16x16x16f16(a, h.b[u], c, 0, 0, 0);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) bits = __builtin_amdgcn_alignbit(bits, __float_as_uint(d[q]), 31);
+        }
+    };
+    // straight-line code per word: all LDS offsets are immediates
+#pragma unroll
+    for (int w = 0; w < kWords; ++w) {
+        uint32_t bits = 0;
+        if (nblk > 8 * w) {  // uniform
+            four(2 * w, bits);
+            if (nblk > 8 * w + 4) four(2 * w + 1, bits);  // may run past nblk: padding
+            else bits <<= 16;
+        }
+        wd[w] = bits;
+    }
+}
+
+// Accept words of one span of a chunk of 11..32 home atoms, in the walk's
+// layout. x, y, z: this lane's home atom (frame); g0: the span's first
+// candidate of each slice, nblk: its blocks (per half with two slices). wd2:
+// the words of the second half (two slices).
+__device__ __forceinline__ void screen_home(const SimArgs& a, const float4* tile, const HomeLanes& hl, int nh, int g0,
+                                            int nblk, float x, float y, float z, float bound16,
+                                            uint32_t (&wd)[kWords], uint32_t (&wd2)[kWords]) {
+    const int lane = lane_here();
+    const int q = lane & 3, r = (lane >> 2) & 3;  // this lane's row of A: candidate q of row group r
+    const int gq = g0 + 4 * (lane >> 4) + q;      // ... of the block of its lane group
+    const float vx = x * a.inv_s, vy = y * a.inv_s, vz = z * a.inv_s;
+    if (hl.ns == 4) {
+        screen_mfma<4>(tile + 4 * gq + r, nblk, a.inv_s, home_ops(vx, vy, vz, hl.act, bound16), wd);
+        return;
+    }
+    const int part = hl.ns == 2 ? r >> 1 : 0, slice = hl.ns == 2 ? r & 1 : r;
+    const float4* base = tile + hl.ns * (gq + 4 * nblk * part) + slice;
+    // atom h's words lie in lane h % 16 + 16 (row group of its slice and half)
+    const int src = (hl.h & 15) + 16 * (hl.act ? hl.s : 0);
+#pragma unroll
+    for (int w = 0; w < kWords; ++w) wd[w] = wd2[w] = 0;
+    for (int e0 = 0; e0 < nh; e0 += 16) {  // two groups of columns
+        const int e = e0 + (lane & 15);  // lane e holds atom e (slice 0)
+        const HomeOps ops = home_ops(from_lane(vx, e), from_lane(vy, e), from_lane(vz, e), e < nh, bound16);
+        uint32_t v[kWords];
+        if (hl.ns == 3) screen_mfma<3>(base, nblk, a.inv_s, ops, v);
+        else screen_mfma<2>(base, nblk, a.inv_s, ops, v);
+        const bool mine = hl.act && (hl.h & ~15) == e0;
+#pragma unroll
+        for (int w = 0; w < kWords; ++w) {
+            const uint32_t lo = from_lane(v[w], src);
+            wd[w] = mine ? lo : wd[w];
+            if (hl.ns == 2) {
+                const uint32_t hi = from_lane(v[w], src + 32);
+                wd2[w] = mine ? hi : wd2[w];
+            }
+        }
+    }
+}
+
+// The 32-bit form for 11..16 atoms, for the pass that writes neighbour lists:
+// what it accepts is what the lists hold, in their order, so its bound is the
+// list radius without the 16-bit margin. A's rows are the candidates' (x, y, z,
+// |x|^2), B's columns (-2 x_i, -2 y_i, -2 z_i, 1) and C = -(bound - |x_i|^2):
+// lane l supplies B[l / 16][l % 16] and A[l % 16][l / 16].
+__device__ __forceinline__ void screen_home32(const float4* tile, const HomeLanes& hl, int g0, int nblk, float x,
+                                              float y, float z, float bound, uint32_t (&wd)[kWords]) {
+    const int lane = lane_here();
+    const int comp = lane >> 4;
+    const int q = lane & 3, r = (lane >> 2) & 3;
+    const float* base = reinterpret_cast<const float*>(tile + 4 * (g0 + q) + r) + comp;
+    const float ai = fmaf(z, z, fmaf(y, y, x * x));
+    const float bval = comp == 3 ? 1.0f : (hl.act ? -2.0f * (comp == 0 ? x : (comp == 1 ? y : z)) : 0.0f);
+    const float cneg = hl.act ? -(bound - ai) : __builtin_huge_valf();
+    const mfma_f4 c = {cneg, cneg, cneg, cneg};
+#pragma unroll
+    for (int w = 0; w < kWords; ++w) {
+        uint32_t bits = 0;
+        const int nb = min(8, nblk - 8 * w);  // uniform
+        if (nb > 0) {
+            for (int b0 = 0; b0 < nb; b0 += 4) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const mfma_f4 d = __builtin_amdgcn_mfma_f32_16x16x4f32(base[(8 * w + b0 + u) * 64], bval, c, 0, 0, 0);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) bits = __builtin_amdgcn_alignbit(bits, __float_as_uint(d[k]), 31);
+                }
+            }
+            const int done = (nb + 3) / 4 * 4;  // blocks shifted in (the last four may run past nb)
+            if (done < 8) bits <<= (32 - 4 * done);
+        }
+        wd[w] = bits;
+    }
+}
+
+// Drop the verdicts past the first n candidates (uniform) of a lane's words.
+__device__ __forceinline__ void keep_first(int n, uint32_t (&wd)[kWords]) {
+#pragma unroll
+    for (int w = 0; w < kWords; ++w) {
+        const int valid = n - 32 * w;
+        wd[w] &= valid >= 32 ? ~0u : (valid <= 0 ? 0u : ~0u << (32 - valid));
+    }
+}
+
 // The LDS byte address of a pointer into shared memory (the low half of its
 // generic address), and a 16-byte load from such an address: walks that
 // carry absolute LDS addresses read their candidates with no add.
@@ -576,280 +894,196 @@ __device__ __forceinline__ float4 lds_load(uint32_t addr) {
     const lds_float4 v = *(const __attribute__((address_space(3))) lds_float4*)(static_cast<uintptr_t>(addr));
     return make_float4(v.x, v.y, v.z, v.w);
 }
+// Marks a loaded value as used here: its register then stays its own until
+// this point. (A candidate's w is read by nobody; reused while the load is in
+// flight, its register would make the wavefront wait for that load first.)
+__device__ __forceinline__ void keep(float v) { asm volatile("" ::"v"(v)); }
 
-// Walk the accepted bits of one span in order, calling op(address, live) for
-// each: address is the LDS byte address of the accepted candidate, the span's
-// candidate 0 lying at wb0; live is false for lanes that have spent their
-// bits. The words rotate through four registers (never indexed, which would
-// put them in scratch memory); an exhausted word is replaced by the next one
-// without a branch. Each iteration takes two candidates (the second may come from the
-// next word), so the wave-wide loop test and branch run once per pair; the
-// calls keep the one-at-a-time order, so sums do not depend on the
-// unrolling.
-template <class Op>
-__device__ __forceinline__ void walk_bits(int ns, uint32_t wb0, uint32_t m, uint32_t n1, uint32_t n2, uint32_t n3,
-                                          Op& op) {
-    const uint32_t cstep = static_cast<uint32_t>(ns) * sizeof(float4);   // bytes between candidates
-    const uint32_t wstep = 32u * cstep;                                  // bytes between words
-    uint32_t wb = wb0;                                                   // LDS address of the word's candidate 0
-    uint32_t left = __builtin_popcount(m) + __builtin_popcount(n1) + __builtin_popcount(n2) +
-                    __builtin_popcount(n3);
-    if (!__any(left != 0u)) return;
-    do {
-        uint32_t off[2];
-        bool live[2];
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const bool next = (m == 0u);
-            m = next ? n1 : m;
-            n1 = next ? n2 : n1;
-            n2 = next ? n3 : n2;
-            n3 = next ? 0u : n3;
-            wb = next ? wb + wstep : wb;
-            live[u] = m != 0u;
-            // all ones for a spent lane (m = 0): its shift clears no bit of
-            // m, and its offset is replaced below
-            const uint32_t k = __builtin_clzg(m, -1);
-            m &= ~(0x80000000u >> (k & 31u));
-            left -= live[u] ? 1u : 0u;
-            // a spent lane keeps rotating (wb grows past its span): it reads
-            // its span's first candidate instead, which is always staged
-            // (a constant stride, as the matrix-core screen's four slices
-            // give, makes the product one shift-and-add; otherwise the 24-bit
-            // multiply-add; either is garbage for a spent lane, replaced here)
-            const uint32_t step = __builtin_constant_p(cstep) ? k * cstep : __umul24(k, cstep);
-            off[u] = live[u] ? wb + step : wb0;
-        }
-        op(off[0], live[0]);
-        op(off[1], live[1]);
-    } while (__any(left != 0u));
+// Largest value of any lane, uniform.
+__device__ __forceinline__ int wave_max(int v) {
+    auto ror = [](int x, auto ctrl) {
+        return max(x, __builtin_amdgcn_update_dpp(x, x, decltype(ctrl)::value, 0xf, 0xf, false));
+    };
+    v = ror(v, std::integral_constant<int, 0x128>{});  // row_ror: 8, 4, 2, 1
+    v = ror(v, std::integral_constant<int, 0x124>{});
+    v = ror(v, std::integral_constant<int, 0x122>{});
+    v = ror(v, std::integral_constant<int, 0x121>{});
+    return max(max(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
+               max(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
 }
 
-// Clear the screen bit of the home atom itself (tile index self_t) if it lies
-// in this lane's span: span candidates are first + g * ns for g < groups.
-__device__ __forceinline__ void clear_self(int self_t, int first, int ns, int groups, uint32_t (&wd)[kWords]) {
-    const int off = self_t - first;
-    if (off < 0 || off % ns != 0) return;
-    const int g = off / ns;
-    if (g >= groups) return;
-    const uint32_t bit = 0x80000000u >> (g & 31);
-    const int w = g >> 5;
-    wd[0] &= (w == 0) ? ~bit : ~0u;
-    wd[1] &= (w == 1) ? ~bit : ~0u;
-    wd[2] &= (w == 2) ? ~bit : ~0u;
-    wd[3] &= (w == 3) ? ~bit : ~0u;
-}
-
-// ---- screen on the matrix cores ------------------------------------------
-// For a home cell of 11..16 atoms the screen runs as 16 x 16 x 4 FP32
-// matrix products: D = A B + C with A the 16 candidates of a block (rows:
-// x, y, z, |x|^2 in the home frame), B the 16 home atoms (columns:
-// -2 x_i, -2 y_i, -2 z_i, 1) and C = -(bound - |x_i|^2) per column, so that
-// D[j][i] = |x_j|^2 - 2 x_i.x_j - (bound - |x_i|^2) = r^2 - bound, negative
-// iff accepted. Lane l supplies B[l / 16][l % 16] and A[l % 16][l / 16],
-// where row m of A is candidate 4 (m % 4) + m / 4 of the block, and receives
-// D[4 (l / 16) + q][l % 16], q = 0..3: lane (home atom l % 16, slice
-// s = l / 16) gets the verdicts on candidates 16 b + 4 q + s of every block
-// b, four sign bits per block, one v_alignbit each (about one VALU
-// instruction per candidate instead of five). A lane's bits thus follow its
-// candidates s, s + 4, s + 8, ... in order: the words are those of the VALU
-// screen with ns = 4 slices, and the same walk takes them. Unused home
-// columns carry C = +inf and B = (0, 0, 0, 1): their D is +inf. Padding
-// entries (w = +inf) are never accepted either.
-constexpr int kMfmaMinHome = 11;  // below this the VALU screen's extra slices win
-typedef float mfma_f4 __attribute__((ext_vector_type(4)));
-
-// Screen one span of nblk <= 32 blocks starting at candidate first (a
-// multiple of 16): word w, bit 31 - k holds the verdict on the lane's
-// candidate first + 4 (32 w + k) + s. bval: this lane's B element; cneg: C.
-__device__ __forceinline__ void screen_mfma(const float4* tile, int first, int nblk, float bval, float cneg,
-                                            uint32_t (&wd)[kWords]) {
-    const int lane = __lane_id();
-    const int row = lane & 15;  // A row: candidate 4 (row % 4) + row / 4 of each block
-    const float* base = reinterpret_cast<const float*>(tile + first) + (4 * (row & 3) + (row >> 2)) * 4 + (lane >> 4);
-    const mfma_f4 c = {cneg, cneg, cneg, cneg};
-#pragma unroll
-    for (int w = 0; w < kWords; ++w) {
-        uint32_t bits = 0;
-        const int nb = min(8, nblk - 8 * w);  // uniform
-        if (nb > 0) {
-            for (int b0 = 0; b0 < nb; b0 += 4) {
-                float av[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) av[u] = base[(8 * w + b0 + u) * 64];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const mfma_f4 d = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u], bval, c, 0, 0, 0);
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) bits = __builtin_amdgcn_alignbit(bits, __float_as_uint(d[q]), 31);
-                }
-            }
-            const int done = (nb + 3) / 4 * 4;  // blocks shifted in (the last group may run past nb)
-            if (done < 8) bits <<= (32 - 4 * done);
-        }
-        wd[w] = bits;
+// The accepted candidates of one set of words in order, as LDS byte addresses:
+// the word's candidate 0 lies at wb, candidates cstep bytes apart. A lane that
+// has spent its bits gets pad, the address of the padding entry past every
+// staged atom. The words rotate through four registers (never indexed, which
+// would put them in scratch memory); an exhausted word is replaced by the next
+// one without a branch.
+struct BitWalk {
+    uint32_t wb, wstep, cstep, pad, m, n1, n2, n3;
+    __device__ __forceinline__ uint32_t next() {
+        const bool turn = (m == 0u);
+        m = turn ? n1 : m;
+        n1 = turn ? n2 : n1;
+        n2 = turn ? n3 : n2;
+        n3 = turn ? 0u : n3;
+        wb += turn ? wstep : 0u;
+        // all ones for a spent lane (m = 0): its shift clears no bit of m, and
+        // its address (16 bits of ones times 16 to 256 bytes, which cannot
+        // wrap) lies past the padding entry
+        const uint32_t k = __builtin_clzg(m, -1);
+        m &= ~(0x80000000u >> (k & 31u));
+        uint32_t at;
+        if (__builtin_constant_p(cstep) && cstep == 64) asm("v_mad_u32_u16 %0, %1, 64, %2" : "=v"(at) : "v"(k), "v"(wb));
+        else asm("v_mad_u32_u16 %0, %1, %2, %3" : "=v"(at) : "v"(k), "s"(cstep), "v"(wb));
+        return min(at, pad);
     }
-}
-
-// ---- neighbourhood of a cell on an x face as x-row pieces -------------------
-// The 27-cell neighbourhood is nine x-rows (dy, dz). In each row the cells
-// that need no image shift in x are consecutive in the sorted arrays (piece A:
-// three cells, or two for a home cell on an x face); on an x face the row's
-// third cell wraps around the box (piece B, one cell, shifted by -+L in x).
-// Interior cells take the scalar row table RowHood; this one, for the cells on
-// the x faces, stages them in one pass too instead of through the LDS segment
-// table of 27 single cells.
-// Pieces are staged in the order A0..A8, B0..B8, so the tile holds the
-// neighbourhood without gaps. The piece table is held one piece per lane
-// (lane k < 9: Ak, lane 9 + k: Bk); the rest is uniform.
-struct RowPieces {
-    int first = 0, pos = 0, len = 0;  // this lane's piece: sorted slot and tile index of its first atom, length
-    int total, home_first, n_home, home_pos;
-    float ox, oy, oz;   // home-cell origin
-    float fxb;          // frame offset in x of the B pieces
-    float fy[3], fz[3];  // frame offsets o - sh of rows with dy, dz = -1, 0, 1
-    bool face;
 };
 
-// Fill r for home cell c (local index, uniform). Lane k < 9 reads the CSR
-// offsets of row k's piece A (four consecutive entries: the start array has
-// four entries of padding after its end) and, on a face, of its piece B.
-__device__ __forceinline__ void row_pieces(const SimArgs& a, int c, RowPieces& r) {
-#pragma clang fp contract(off)
-    const int lane = __lane_id();
-    const int nc = a.nc;
-    const int nn = nc * nc;
-    const int iz = c / nn;
-    const int rem = c - iz * nn;
-    const int iy = rem / nc;
-    const int ix = rem - iy * nc;
-    r.face = ix == 0 || ix == nc - 1;
-    r.ox = static_cast<float>(ix) * a.s;
-    r.oy = static_cast<float>(iy) * a.s;
-    r.oz = static_cast<float>(iz) * a.s;
-    r.fy[0] = iy == 0 ? r.oy + a.box : r.oy;
-    r.fy[1] = r.oy;
-    r.fy[2] = iy == nc - 1 ? r.oy - a.box : r.oy;
-    r.fz[0] = iz == 0 ? r.oz + a.box : r.oz;
-    r.fz[1] = r.oz;
-    r.fz[2] = iz == nc - 1 ? r.oz - a.box : r.oz;
-    r.fxb = ix == 0 ? r.ox + a.box : r.ox - a.box;
-    // first cell of piece A; the home cell is cell hoff of it (0 or 1)
-    const int a0 = ix == 0 ? 0 : (ix == nc - 1 ? nc - 2 : ix - 1);
-    const int hoff = ix - a0;
-    const int bcell = ix == 0 ? nc - 1 : 0;
-    Int4u row = {0, 0, 0, 0};
-    int b0 = 0, b1 = 0;
-    if (lane < 9) {
-        int jy = iy + lane % 3 - 1, jz = iz + lane / 3 - 1;
-        jy = jy < 0 ? jy + nc : (jy >= nc ? jy - nc : jy);
-        jz = jz < 0 ? jz + nc : (jz >= nc ? jz - nc : jz);
-        const int* rs = a.start + a.cbase + nc * (jy + nc * jz);
-        row = *reinterpret_cast<const Int4u*>(rs + a0);
-        if (r.face) {
-            b0 = rs[bcell];
-            b1 = rs[bcell + 1];
-        }
+// Walk a lane's accept words, op(op.load(address)) for each candidate in
+// order, two per step: the next two candidates' loads are issued before this
+// step's arithmetic, so their latency is covered (two register sets take
+// turns, which saves copying them). The trip count is the busiest lane's,
+// reduced once, so the loop needs no test on the lanes.
+template <class Op>
+__device__ __forceinline__ void walk_bits(int ns, uint32_t wb0, uint32_t pad, const uint32_t (&wd)[kWords], Op& op) {
+    const uint32_t cstep = static_cast<uint32_t>(ns) * sizeof(float4);
+    // a lane's steps: its bits, and one for each empty word before its last bit
+    int steps = __builtin_popcount(wd[3]);
+#pragma unroll
+    for (int w = kWords - 2; w >= 0; --w) steps += max(__builtin_popcount(wd[w]), min(steps, 1));
+    const int trips = wave_max(steps);
+    if (trips == 0) return;
+    BitWalk b{wb0, 32u * cstep, cstep, pad, wd[0], wd[1], wd[2], wd[3]};
+    auto load = [&](typename Op::Entry (&q)[2]) {
+        const uint32_t a0 = b.next(), a1 = b.next();
+        q[0] = op.load(a0);
+        q[1] = op.load(a1);
+    };
+    typename Op::Entry p[2], q[2];
+    load(p);
+    int sets = (trips + 1) >> 1;  // pairs of candidates still to take, p's among them
+    for (; sets > 2; sets -= 2) {
+        load(q);
+        op(p[0]);
+        op(p[1]);
+        load(p);
+        op(q[0]);
+        op(q[1]);
     }
-    const int aend = r.face ? row.z : row.w;
-    if (lane < 9) {
-        r.first = row.x;
-        r.len = aend - row.x;
+    if (sets == 2) load(q);
+    op(p[0]);
+    op(p[1]);
+    if (sets == 2) {
+        op(q[0]);
+        op(q[1]);
     }
-    if (r.face) {  // B pieces to lanes 9..17
-        const int src = lane >= 9 && lane < 18 ? lane - 9 : 0;
-        const int bf = __shfl(b0, src), bl = __shfl(b1 - b0, src);
-        if (lane >= 9 && lane < 18) {
-            r.first = bf;
-            r.len = bl;
-        }
-    }
-    const int incl = wave_incl_scan(r.len);
-    r.pos = incl - r.len;
-    r.total = __builtin_amdgcn_readlane(incl, 17);
-    const int hb = hoff == 0 ? row.x : row.y, he = hoff == 0 ? row.y : row.z;
-    r.home_first = __builtin_amdgcn_readlane(hb, 4);
-    r.n_home = __builtin_amdgcn_readlane(he, 4) - r.home_first;
-    r.home_pos = __builtin_amdgcn_readlane(r.pos, 4) + (r.home_first - __builtin_amdgcn_readlane(r.first, 4));
 }
 
-// Staging of nine pieces (table lanes k0 .. k0 + 8) in one pass by the
-// unmasked scheme of stage_whole: every lane loads and stores entry
-// pos + lane of each piece; pieces are written in order, so a piece's surplus
-// entries are overwritten by a later piece or fall into the padding after the
-// total. Atoms 64 and up of a longer piece follow, masked. SECOND as for
-// stage_rows.
-template <int K0, int SECOND>
-__device__ __forceinline__ void stage_nine(const SimArgs& a, const RowPieces& r, float fx, float4* tile,
-                                           float4* raw, const float4* vsrc) {
-    const int lane = __lane_id();
-    const int last = a.natoms - 1;
-    const char* pbase = reinterpret_cast<const char*>(a.pos0);
-    const char* vbase = reinterpret_cast<const char*>(vsrc);
-    float4 q[9];
+// Clear the screen bit of the home atom itself: g is its number among the
+// words' candidates, if it lies in this lane's slice (own). The atoms of a cell
+// are neighbours in the tile, so one or two words are touched: each is skipped
+// unless some lane's bit lies in it.
+__device__ __forceinline__ void clear_self(int g, bool own, uint32_t (&wd)[kWords]) {
+    const uint32_t bit = 0x80000000u >> (g & 31);
+    const int w = own ? g >> 5 : -1;
 #pragma unroll
-    for (int k = 0; k < 9; ++k) {
-        const uint32_t off = static_cast<uint32_t>(min(__builtin_amdgcn_readlane(r.first, K0 + k) + lane, last)) << 4;
-        q[k] = *reinterpret_cast<const float4*>(pbase + off);
-    }
-    uint32_t* codes = reinterpret_cast<uint32_t*>(raw);
-    const int sx = SECOND == SECOND_CODE ? image_shift(r.ox, fx, a.box) : 0;
-#pragma unroll
-    for (int k = 0; k < 9; ++k) {
-        const float x = q[k].x - fx;
-        const float y = q[k].y - r.fy[k % 3];
-        const float z = q[k].z - r.fz[k / 3];
-        const int p = __builtin_amdgcn_readlane(r.pos, K0 + k);
-        tile[p + lane] = make_float4(x, y, z, x * x + y * y + z * z);
-        if (SECOND == SECOND_RAW) raw[p + lane] = q[k];
-        if (SECOND == SECOND_CODE)
-            codes[p + lane] = list_entry(__builtin_amdgcn_readlane(r.first, K0 + k) + lane, sx,
-                                         image_shift(r.oy, r.fy[k % 3], a.box), image_shift(r.oz, r.fz[k / 3], a.box));
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    if (SECOND == SECOND_VEC) {  // a second round (the positions' registers are free again)
-#pragma unroll
-        for (int k = 0; k < 9; ++k) {
-            const uint32_t off = static_cast<uint32_t>(min(__builtin_amdgcn_readlane(r.first, K0 + k) + lane, last))
-                                 << 4;
-            q[k] = *reinterpret_cast<const float4*>(vbase + off);
+    for (int i = 0; i < kWords; ++i)
+        if (__any(w == i)) wd[i] &= w == i ? ~bit : ~0u;
+}
+
+// One pass over the tn staged candidates for a chunk of nh home atoms: fn(wd,
+// first, n) for every set of accept words (this lane's n-th candidate is tile
+// entry first + n ns; n: candidates of the largest slice in the set), with the
+// home atom's own bit cleared. x, y, z: this lane's home atom in the frame;
+// bound, bound16: the screens' bounds (EXACT: only the first is used);
+// self_t: its tile index (may be outside); wv, nw: this wavefront takes the
+// wv-th of nw contiguous ranges of the candidates. kept(wd, n): true if it
+// supplied the words itself.
+template <bool EXACT, class Kept, class Fn>
+__device__ __forceinline__ void for_each_words(const SimArgs& a, const float4* tile, int tn, const HomeLanes& hl,
+                                               int nh, float x, float y, float z, float bound, float bound16,
+                                               int self_t, int wv, int nw, Kept kept, Fn fn) {
+    const int ns = hl.ns;
+    const bool four = nh >= kMfmaMinHome && nh <= 16;
+    const bool mat = nh >= kMfmaMinHome && nh <= (EXACT ? 16 : kMfmaMaxHome);  // uniform
+    // this wavefront's candidates [g_lo, g_hi) of every slice, split at
+    // multiples of the screen's step (so no verdict is taken twice): 16 with
+    // four slices, else four
+    int g_lo = 0, g_hi;
+    if (four) {
+        const int nblk = (tn + 15) / 16;
+        g_hi = 4 * nblk;
+        if (nw > 1) {
+            const int q4 = (nblk + 3) >> 2;
+            g_lo = 16 * ((q4 * wv) / nw);
+            g_hi = min(g_hi, 16 * ((q4 * (wv + 1)) / nw));
         }
-#pragma unroll
-        for (int k = 0; k < 9; ++k) {
-            raw[__builtin_amdgcn_readlane(r.pos, K0 + k) + lane] = q[k];
-            __builtin_amdgcn_sched_barrier(0);
+    } else {
+        g_hi = (tn + ns - 1) / ns;
+        if (nw > 1) {
+            const int q4 = (g_hi + kScreenUnroll - 1) / kScreenUnroll;
+            g_lo = kScreenUnroll * ((q4 * wv) / nw);
+            g_hi = min(g_hi, kScreenUnroll * ((q4 * (wv + 1)) / nw));
         }
     }
-    if (__any(lane >= K0 && lane < K0 + 9 && r.len > kWave)) {  // rare
-#pragma unroll
-        for (int k = 0; k < 9; ++k) {
-            const int len = __builtin_amdgcn_readlane(r.len, K0 + k);
-            if (len > kWave) {
-                const int f = __builtin_amdgcn_readlane(r.first, K0 + k), p = __builtin_amdgcn_readlane(r.pos, K0 + k);
-                for (int off = kWave + lane; off - lane < len; off += kWave) {
-                    if (off < len) {
-                        const float4 u = a.pos0[f + off];
-                        const float x = u.x - fx, y = u.y - r.fy[k % 3], z = u.z - r.fz[k / 3];
-                        tile[p + off] = make_float4(x, y, z, x * x + y * y + z * z);
-                        if (SECOND == SECOND_RAW) raw[p + off] = u;
-                        if (SECOND == SECOND_VEC) raw[p + off] = vsrc[f + off];
-                        if (SECOND == SECOND_CODE)
-                            codes[p + off] = list_entry(f + off, sx, image_shift(r.oy, r.fy[k % 3], a.box),
-                                                        image_shift(r.oz, r.fz[k / 3], a.box));
-                    }
+    if (mat) {
+        const int span = ns == 2 ? 2 * kGroups : kGroups;
+        for (int g0 = g_lo; g0 < g_hi; g0 += span) {
+            const int groups = min(span, g_hi - g0);
+            const int blocks = (groups + 3) >> 2;
+            // per half: whole steps of the screen (four blocks), so the first
+            // half does not run into the second
+            const int nblk = ns == 2 ? ((blocks + 7) >> 3) << 2 : blocks;
+            uint32_t wd[kWords], wd2[kWords];
+            const int n1 = min(groups, 4 * nblk);
+            const bool had = kept(wd, n1);
+            if (!had) {
+                if (EXACT) screen_home32(tile, hl, g0, nblk, x, y, z, bound, wd);
+                else screen_home(a, tile, hl, nh, g0, nblk, x, y, z, bound16, wd, wd2);
+                if (nw > 1 && !four) keep_first(n1, wd);  // the screen's last step may be the next range's
+                // the home atom's own slice and number, from its tile index
+                const int c = self_t - g0 * ns;
+                if (EXACT || four) {
+                    clear_self(c >> 2, (c & 3) == hl.s, wd);
+                } else if (c >= 0) {
+                    const int g = ns == 3 ? static_cast<int>((static_cast<uint32_t>(c) * 43691u) >> 17) : c >> 1;
+                    const bool own = hl.act && c - g * ns == hl.s;
+                    clear_self(g < 4 * nblk ? g : -1, own, wd);
+                    if (ns == 2) clear_self(g - 4 * nblk, own, wd2);
                 }
             }
+            const int first = g0 * ns + (hl.act ? hl.s : 0);
+            fn(wd, first, n1, had);
+            if (!EXACT && ns == 2 && groups > n1) {
+                if (!had) keep_first(groups - n1, wd2);  // likewise
+                const bool had2 = kept(wd2, groups - n1);
+                fn(wd2, first + 4 * nblk * ns, groups - n1, had2);
+            }
         }
+        return;
     }
-}
-
-// The whole neighbourhood of r in one pass (total <= tile capacity; the tile
-// needs room for total + 63 entries).
-template <int SECOND = SECOND_NONE>
-__device__ __forceinline__ void stage_pieces(const SimArgs& a, const RowPieces& r, float4* tile, float4* raw = nullptr,
-                                             const float4* vsrc = nullptr) {
-    stage_nine<0, SECOND>(a, r, r.ox, tile, raw, vsrc);
-    if (r.face) stage_nine<9, SECOND>(a, r, r.fxb, tile, raw, vsrc);
+    const float ai = fmaf(z, z, fmaf(y, y, x * x));
+    // idle lanes get a bound no candidate can meet (q.w - thr_i = +inf)
+    const float thr_i = hl.act ? bound - ai : -__builtin_huge_valf();
+    const float mx = -2.0f * x, my = -2.0f * y, mz = -2.0f * z;
+    for (int g0 = g_lo; g0 < g_hi; g0 += kGroups) {
+        const int groups = min(kGroups, g_hi - g0);
+        const int first = g0 * ns + (hl.act ? hl.s : 0);
+        uint32_t wd[kWords];
+        const bool had = kept(wd, groups);
+        if (!had) {
+            if (ns == 6) screen_span<6>(tile, first, ns, groups, mx, my, mz, thr_i, wd);
+            else screen_span<0>(tile, first, ns, groups, mx, my, mz, thr_i, wd);
+            const int c = self_t - first;
+            if (hl.act && c >= 0) {
+                int d = ns;
+                asm("" : "+s"(d));  // the reciprocal is made here, not ahead of every path
+                const int g = c / d;
+                clear_self(g, g * ns == c, wd);
+            }
+        }
+        fn(wd, first, groups, had);
+    }
 }
 
 }  // namespace

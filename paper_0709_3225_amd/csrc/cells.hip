@@ -64,7 +64,7 @@ __global__ void __launch_bounds__(kBlock) k_zero_blocks(SimArgs a, int par) {
 // lanes past the end); cells are numbered globally (a.cbase + local index).
 __device__ __forceinline__ void load_atom(const SimArgs& a, int i, bool valid, const float4* __restrict__ pos_in,
                                           const float4* __restrict__ vel_in) {
-    const float invL = 1.0f / a.box;
+    const float invL = a.inv_box;
     int c = -1;
     float4 p = make_float4(0.f, 0.f, 0.f, 0.f), v = make_float4(0.f, 0.f, 0.f, 0.f);
     if (valid) {

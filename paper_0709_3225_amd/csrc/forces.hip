@@ -23,12 +23,11 @@ namespace {
 
 template <bool ENERGY>
 __device__ __forceinline__ float pair_force(const SimArgs& a, const float4 q, float xi, float yi, float zi,
-                                            bool live, float& fx, float& fy, float& fz, float& u_loc,
-                                            float& w_loc) {
+                                            bool in, float& fx, float& fy, float& fz, float& u_loc, float& w_loc) {
     const float dx = xi - q.x, dy = yi - q.y, dz = zi - q.z;
     const float r2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
     // the atom itself never reaches this point (its screen bit is cleared)
-    const bool ok = live && (r2 < a.rc2);
+    const bool ok = in && (r2 < a.rc2);
     const float rinv = __builtin_amdgcn_rsqf(r2);
     const float ir2 = rinv * rinv;
     const float ir6 = ir2 * ir2 * ir2;
@@ -47,15 +46,17 @@ __device__ __forceinline__ float pair_force(const SimArgs& a, const float4 q, fl
     return r2;
 }
 
-// Pair operation of the force walk: the accepted candidate at an LDS address.
+// Pair operation of the force walk (the padding entry fails the cutoff test).
 template <bool ENERGY>
 struct ForceOp {
     const SimArgs& a;
     float xi, yi, zi;
     float fx = 0.f, fy = 0.f, fz = 0.f, u_loc = 0.f, w_loc = 0.f;
-    __device__ __forceinline__ void operator()(uint32_t addr, bool live) {
-        const float4 q = lds_load(addr);
-        pair_force<ENERGY>(a, q, xi, yi, zi, live, fx, fy, fz, u_loc, w_loc);
+    using Entry = float4;
+    __device__ __forceinline__ Entry load(uint32_t addr) const { return lds_load(addr); }
+    __device__ __forceinline__ void operator()(const Entry& q) {
+        keep(q.w);
+        pair_force<ENERGY>(a, q, xi, yi, zi, true, fx, fy, fz, u_loc, w_loc);
     }
 };
 
@@ -66,18 +67,25 @@ template <bool ENERGY>
 struct RecordOp {
     const SimArgs& a;
     uint32_t tile0;     // LDS address of the tile
+    uint32_t pad;       // and of the padding entry after the staged atoms
     const char* cbase;  // list entries of the staged atoms (4 bytes each, at a quarter of the tile's offsets)
     float xi, yi, zi;
     uint32_t* row;      // the home atom's list: entry k at row[4 n (k / 4) + k % 4]
     int next;
     float fx = 0.f, fy = 0.f, fz = 0.f, u_loc = 0.f, w_loc = 0.f;
-    __device__ __forceinline__ void operator()(uint32_t addr, bool live) {
-        const float4 q = lds_load(addr);
-        pair_force<ENERGY>(a, q, xi, yi, zi, live, fx, fy, fz, u_loc, w_loc);
-        if (live) {
-            if (next < a.nlist_cap)
-                row[4 * static_cast<size_t>(a.n) * (next >> 2) + (next & 3)] =
-                    *reinterpret_cast<const uint32_t*>(cbase + ((addr - tile0) >> 2));
+    struct Entry {
+        float4 q;
+        uint32_t code;
+        bool live;  // not a spent lane
+    };
+    __device__ __forceinline__ Entry load(uint32_t addr) const {
+        return Entry{lds_load(addr), *reinterpret_cast<const uint32_t*>(cbase + ((addr - tile0) >> 2)), addr < pad};
+    }
+    __device__ __forceinline__ void operator()(const Entry& e) {
+        keep(e.q.w);
+        pair_force<ENERGY>(a, e.q, xi, yi, zi, true, fx, fy, fz, u_loc, w_loc);
+        if (e.live) {
+            if (next < a.nlist_cap) row[4 * static_cast<size_t>(a.n) * (next >> 2) + (next & 3)] = e.code;
             ++next;
         }
     }
@@ -101,13 +109,17 @@ struct ExportOp {
     int idi;
     const ExportArgs& ex;
     bool over = false;
-    __device__ __forceinline__ void operator()(uint32_t addr, bool live) {
-        const uint32_t off = addr - tile0;
-        const float4 q = lds_load(addr);
+    struct Entry {
+        float4 q;
+        uint32_t off;  // from the tile
+    };
+    __device__ __forceinline__ Entry load(uint32_t addr) const { return Entry{lds_load(addr), addr - tile0}; }
+    __device__ __forceinline__ void operator()(const Entry& e) {
+        const float4 q = e.q;
         const float dx = xi - q.x, dy = yi - q.y, dz = zi - q.z;
         const float r2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
-        if (live && r2 < a.rc2) {
-            const int idj = __float_as_int(reinterpret_cast<const float4*>(rbase + off)->w);
+        if (r2 < a.rc2) {
+            const int idj = __float_as_int(reinterpret_cast<const float4*>(rbase + e.off)->w);
             const int slot = atomicAdd(&ex.counts[idi], 1);
             if (slot < ex.max_nb) ex.idx[static_cast<size_t>(idi) * ex.max_nb + slot] = idj;
             else over = true;
@@ -115,15 +127,16 @@ struct ExportOp {
     }
 };
 
-// Kept accept words (pair lists as bitmasks): span j of a lane is one 16-byte
-// record; spans past kListSpans are only counted (the cell then screens).
+// Kept accept words (pair lists as bitmasks): each set of a lane's words is one
+// 16-byte record; sets past kListSpans are only counted (the cell then
+// screens).
 __device__ __forceinline__ void keep_words(uint4* rows, int& n, const uint32_t (&wd)[kWords]) {
     if (n < kListSpans) rows[n] = make_uint4(wd[0], wd[1], wd[2], wd[3]);
     ++n;
 }
 
-// Span j's kept words; span 0 was requested before the staging (w0). Bits
-// past the span's groups candidates per lane are dropped, so a walk never
+// Record j of the kept words; record 0 was requested before the staging (w0).
+// Bits past the set's groups candidates per lane are dropped, so a walk never
 // leaves the staged span, whatever the words hold.
 __device__ __forceinline__ void kept_words(const uint4* rows, const uint4& w0, int j, int groups,
                                            uint32_t (&wd)[kWords]) {
@@ -132,11 +145,7 @@ __device__ __forceinline__ void kept_words(const uint4* rows, const uint4& w0, i
     wd[1] = v.y;
     wd[2] = v.z;
     wd[3] = v.w;
-#pragma unroll
-    for (int w = 0; w < kWords; ++w) {
-        const int valid = groups - 32 * w;  // uniform
-        wd[w] &= valid >= 32 ? ~0u : (valid <= 0 ? 0u : ~0u << (32 - valid));
-    }
+    keep_first(groups, wd);
 }
 
 // Forces on the atoms of home cell c (local index of the system described by
@@ -178,38 +187,19 @@ __device__ __forceinline__ void force_cell(const SimArgs& a, int c, float4* tile
     const int wv = MW == 1 ? 0 : static_cast<int>(threadIdx.x) >> 6;  // uniform per wavefront
     const int nw = MW == 1 ? 1 : static_cast<int>(blockDim.x) >> 6;
     float ox, oy, oz;
-    // a cell away from the x faces whose neighbourhood and home atoms fit one
-    // pass is staged here, from a table in scalar registers; others take the
-    // LDS table and stage in the pass loop below
+    // a neighbourhood and home atoms that fit one pass are staged here, from a
+    // table in scalar registers; others take the LDS table and stage in the
+    // pass loop below
     RowHood rh;
-    const bool interior = row_hood(a, c, rh);  // uniform
-    bool rows = interior && rh.pos[9] <= a.tile_cap && rh.n_home <= kWave;
-    int total, home_first, n_home, home_pos;
+    row_hood(a, c, rh);
+    const bool rows = rh.total <= a.tile_cap && rh.n_home <= kWave;  // uniform
+    int total = rh.total, home_first = rh.home_first, n_home = rh.n_home, home_pos = rh.home_pos;
+    ox = rh.ox;
+    oy = rh.oy;
+    oz = rh.oz;
     if (rows) {
-        ox = rh.ox;
-        oy = rh.oy;
-        oz = rh.oz;
-        total = rh.pos[9];
-        home_first = rh.home_first;
-        n_home = rh.n_home;
-        home_pos = rh.home_pos;
-        if (wv == 0) stage_rows<EXPORT ? SECOND_RAW : (LIST == 3 ? SECOND_CODE : SECOND_NONE)>(a, rh, tile, raw);
-    }
-    // a cell on an x face: the same one-pass staging from a table of row pieces
-    RowPieces rp;
-    if (!interior) row_pieces(a, c, rp);
-    if (!interior && rp.total <= a.tile_cap && rp.n_home <= kWave) {
-        rows = true;
-        ox = rp.ox;
-        oy = rp.oy;
-        oz = rp.oz;
-        total = rp.total;
-        home_first = rp.home_first;
-        n_home = rp.n_home;
-        home_pos = rp.home_pos;
-        if (wv == 0) stage_pieces<EXPORT ? SECOND_RAW : (LIST == 3 ? SECOND_CODE : SECOND_NONE)>(a, rp, tile, raw);
-    }
-    if (!rows) {
+        if (wv == 0) stage_hood<EXPORT ? SECOND_RAW : (LIST == 3 ? SECOND_CODE : SECOND_NONE)>(a, rh, tile, raw);
+    } else {
         load_neighbourhood(a, c, nb, ox, oy, oz);
         total = nb.total;
         home_first = nb.home_first;
@@ -222,7 +212,7 @@ __device__ __forceinline__ void force_cell(const SimArgs& a, int c, float4* tile
     const size_t lrow = (static_cast<size_t>(a.cbase + c) * kWave + lane);  // this lane's kept words
     uint4* lwords = reinterpret_cast<uint4*>(a.plist) + lrow * kListSpans;
     const bool list_fits = total <= a.tile_cap && n_home <= kWave;          // uniform
-    int n_rec = 0;  // LIST 1: spans kept
+    int n_rec = 0;  // LIST 1, 2: sets of words kept, taken
     int list_n = 0;
     uint4 lw0 = make_uint4(0u, 0u, 0u, 0u);  // LIST 2: the first span's words, requested before staging
     if (LIST == 2) {
@@ -232,36 +222,26 @@ __device__ __forceinline__ void force_cell(const SimArgs& a, int c, float4* tile
     const bool use_list = LIST == 2 && list_fits && __all(list_n <= kListSpans);
     for (int h0 = 0; h0 < n_home; h0 += kWave) {
         const int nh = min(kWave, n_home - h0);
-        // 11..16 home atoms: matrix-core screen, lane = (atom lane % 16, slice
-        // lane / 16); otherwise the VALU screen with ns interleaved slices
-        const bool mf = nh >= kMfmaMinHome && nh <= 16;  // uniform
-        const int ns = mf ? 4 : min(kMaxSlices, kWave / nh);
-        const int hstride = mf ? 16 : nh;  // lanes of one home atom: h, h + hstride, ...
-        const int h = lane % hstride, s = lane / hstride;
-        const bool act = mf ? h < nh : s < ns;
+        const HomeLanes hl = home_lanes(nh);
+        const int ns = hl.ns, hstride = hl.hs, h = hl.h, s = hl.s;
+        const bool act = hl.act;
         // the lane that finishes home atom h (in wavefront 0); in the
-        // matrix-core layout lanes nh..15 have s == 0 but no atom
+        // four-slice layout lanes nh..15 have s == 0 but no atom
         const bool lead = act && s == 0 && wv == 0;
-        float4 pi = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (act) pi = a.pos0[home_first + h0 + h];
+        // (lanes without an atom read past the arrays' end: zeros)
+        const uint32_t at = 16u * static_cast<uint32_t>(home_first + h0 + h), past = ~15u;
+        const float4 pi = load_slot<true>(slot_buffer(a.pos0, a.natoms), act ? at : past);
         float4 vel = make_float4(0.f, 0.f, 0.f, 0.f);  // fetched now, used by the epilogue
-        if ((KICK || ENERGY) && lead) vel = a.vel0[home_first + h0 + h];
+        if (KICK || ENERGY) vel = load_slot<true>(slot_buffer(late_args().vel0, a.natoms), lead ? at : past);
         float4 pref = pi;  // LIST: position when the lists were recorded
         if (LIST == 2 && SKIN && lead) pref = a.posref[home_first + h0 + h];
         if ((LIST == 1 || LIST == 3) && lead) a.posref[home_first + h0 + h] = pi;
         const float xi = pi.x - ox, yi = pi.y - oy, zi = pi.z - oz;
-        const float ai = fmaf(zi, zi, fmaf(yi, yi, xi * xi));
-        // idle lanes get a bound no candidate can meet (q.w - thr_i = +inf)
-        // (the list radius only where the words are kept: other cells sum as the plain screen does)
-        const float thr_i = act ? (((LIST == 1 && list_fits) || LIST == 3) ? a.list_screen2 : a.screen2) - ai
-                                : -__builtin_huge_valf();
-        const float mx = -2.0f * xi, my = -2.0f * yi, mz = -2.0f * zi;
-        // matrix-core operands: this lane's element of B (component s of
-        // (-2 x_i, -2 y_i, -2 z_i, 1)) and of C (-bound + |x_i|^2; +inf idle)
-        const float bval = s == 3 ? 1.0f : (act ? (s == 0 ? mx : (s == 1 ? my : mz)) : 0.0f);
-        const float cneg = -thr_i;
+        // the list radius only where the words are kept: other cells sum as the plain screen does
+        const bool wide = (LIST == 1 && list_fits) || LIST == 3;
+        const float bound = wide ? a.list_screen2 : a.screen2, bound16 = wide ? a.list_screen16 : a.screen16;
         float fx = 0.f, fy = 0.f, fz = 0.f, u_loc = 0.f, w_loc = 0.f;
-        int lcount = 0, rec_next = 0;  // LIST 3: the atom's entries so far; this lane's next one
+        int lcount = 0;  // LIST 3: the atom's entries so far
         uint32_t* lrow_list = LIST == 3 ? a.nlist + 4 * static_cast<size_t>(home_first + h0 + h) : nullptr;
         for (int t0 = 0; t0 < total; t0 += a.tile_cap) {
             const int tn = min(a.tile_cap, total - t0);
@@ -274,32 +254,34 @@ __device__ __forceinline__ void force_cell(const SimArgs& a, int c, float4* tile
                 }
             }
             if (wv == 0)
-                for (int t = lane; t < kTilePad; t += kWave) tile[tn + t] = make_float4(0.f, 0.f, 0.f, __builtin_huge_valf());
+                for (int t = lane; t < kTilePad; t += kWave) tile[tn + t] = pad_entry(a);
             __syncthreads();
             const int self_t = home_pos + h0 + h - t0;  // the home atom's own tile index (may be outside)
-            // the walk over one span's words; the lane's candidates are cand0,
-            // cand0 + ns_, cand0 + 2 ns_, ...
-            // LIST 3: this lane's first entry for the span's accepted
-            // candidates (after those of the atom's lower slices)
-            auto list_base = [&](const uint32_t (&wd)[kWords]) {
-                if (LIST != 3) return;
-                const int cnt = __popc(wd[0]) + __popc(wd[1]) + __popc(wd[2]) + __popc(wd[3]);
-                int pre = 0, tot = 0;
-                for (int q = 0; q < ns; ++q) {
-                    const int v = __shfl(cnt, h + q * hstride);
-                    pre += q < s ? v : 0;
-                    tot += v;
-                }
-                rec_next = lcount + pre;
-                lcount += tot;
+            const uint32_t tile0 = lds_address(tile);
+            const uint32_t pad = tile0 + static_cast<uint32_t>(tn) * sizeof(float4);
+            auto kept = [&](uint32_t (&wd)[kWords], int groups) {
+                if (!(LIST == 2 && use_list)) return false;
+                kept_words(lwords, lw0, n_rec++, groups, wd);
+                return true;
             };
-            auto walk = [&](int ns_, int cand0, uint32_t (&wd)[kWords]) {
-                const uint32_t tile0 = lds_address(tile);
-                const uint32_t wb0 = tile0 + static_cast<uint32_t>(cand0) * sizeof(float4);
+            for_each_words<LIST == 3>(a, tile, tn, hl, nh, xi, yi, zi, bound, bound16, self_t, wv, nw, kept,
+                           [&](uint32_t (&wd)[kWords], int first, int, bool) {
+                if (LIST == 1 && list_fits) keep_words(lwords, n_rec, wd);
+                const uint32_t wb0 = tile0 + static_cast<uint32_t>(first) * sizeof(float4);
                 if (LIST == 3) {
-                    RecordOp<ENERGY> op{a,  tile0, reinterpret_cast<const char*>(raw), xi, yi, zi, lrow_list, rec_next,
-                                        fx, fy, fz, u_loc, w_loc};
-                    walk_bits(ns_, wb0, wd[0], wd[1], wd[2], wd[3], op);
+                    // this lane's first entry for the accepted candidates
+                    // (after those of the atom's lower slices)
+                    const int cnt = __popc(wd[0]) + __popc(wd[1]) + __popc(wd[2]) + __popc(wd[3]);
+                    int pre = 0, tot = 0;
+                    for (int q = 0; q < ns; ++q) {
+                        const int v = __shfl(cnt, h + q * hstride);
+                        pre += q < s ? v : 0;
+                        tot += v;
+                    }
+                    RecordOp<ENERGY> op{a,  tile0, pad, reinterpret_cast<const char*>(raw), xi, yi, zi, lrow_list,
+                                        lcount + pre, fx, fy, fz, u_loc, w_loc};
+                    lcount += tot;
+                    walk_bits(ns, wb0, pad, wd, op);
                     fx = op.fx;
                     fy = op.fy;
                     fz = op.fz;
@@ -307,66 +289,19 @@ __device__ __forceinline__ void force_cell(const SimArgs& a, int c, float4* tile
                     w_loc = op.w_loc;
                 } else if (EXPORT) {
                     ExportOp op{a, tile0, reinterpret_cast<const char*>(raw), xi, yi, zi, __float_as_int(pi.w), ex};
-                    walk_bits(ns_, wb0, wd[0], wd[1], wd[2], wd[3], op);
+                    walk_bits(ns, wb0, pad, wd, op);
                     over = over || op.over;
                 } else {
                     ForceOp<ENERGY> op{a, xi, yi, zi, fx, fy, fz, u_loc, w_loc};
-                    walk_bits(ns_, wb0, wd[0], wd[1], wd[2], wd[3], op);
+                    if (ns == 4) walk_bits(4, wb0, pad, wd, op);
+                    else walk_bits(ns, wb0, pad, wd, op);
                     fx = op.fx;
                     fy = op.fy;
                     fz = op.fz;
                     u_loc = op.u_loc;
                     w_loc = op.w_loc;
                 }
-            };
-            if (mf) {
-                // this wavefront's blocks [b_lo, b_hi), split at multiples of four
-                // blocks (the screen's step), so no verdict is taken twice
-                const int nblk_all = (tn + 15) / 16;
-                const int q4 = (nblk_all + 3) >> 2;
-                const int b_lo = 4 * ((q4 * wv) / nw), b_hi = min(nblk_all, 4 * ((q4 * (wv + 1)) / nw));
-                for (int b0 = b_lo; b0 < b_hi; b0 += 8 * kWords) {
-                    const int nblk = min(8 * kWords, b_hi - b0);
-                    uint32_t wd[kWords];
-                    if (LIST == 2 && use_list) {
-                        kept_words(lwords, lw0, b0 / (8 * kWords), 4 * nblk, wd);
-                    } else {
-                        screen_mfma(tile, 16 * b0, nblk, bval, cneg, wd);
-                        if (act) clear_self(self_t - 16 * b0, s, 4, 4 * nblk, wd);
-                        if (LIST == 1 && list_fits) keep_words(lwords, n_rec, wd);
-                        list_base(wd);
-                    }
-                    // the lane's candidates are tile + 16 b0 + s + 4 g, as for four VALU slices
-                    walk(4, 16 * b0 + s, wd);
-                }
-                continue;
-            }
-            const int groups_all = (tn + ns - 1) / ns;  // candidates of the largest slice
-            // this wavefront's groups [g_lo, g_hi), split at multiples of the screen's step
-            const int q4 = (groups_all + kScreenUnroll - 1) / kScreenUnroll;
-            const int g_lo = kScreenUnroll * ((q4 * wv) / nw);
-            const int g_hi = min(groups_all, kScreenUnroll * ((q4 * (wv + 1)) / nw));
-            for (int g0 = g_lo; g0 < g_hi; g0 += kGroups) {
-                const int groups = min(kGroups, g_hi - g0);
-                const int first = g0 * ns + (act ? s : 0);
-                uint32_t wd[kWords];
-                if (LIST == 2 && use_list) {
-                    kept_words(lwords, lw0, g0 / kGroups, groups, wd);
-                } else {
-                    switch (ns) {
-                        case 2: screen_span<2>(tile, first, ns, groups, mx, my, mz, thr_i, wd); break;
-                        case 3: screen_span<3>(tile, first, ns, groups, mx, my, mz, thr_i, wd); break;
-                        case 4: screen_span<4>(tile, first, ns, groups, mx, my, mz, thr_i, wd); break;
-                        case 5: screen_span<5>(tile, first, ns, groups, mx, my, mz, thr_i, wd); break;
-                        case 6: screen_span<6>(tile, first, ns, groups, mx, my, mz, thr_i, wd); break;
-                        default: screen_span<0>(tile, first, ns, groups, mx, my, mz, thr_i, wd); break;
-                    }
-                    if (act) clear_self(self_t, first, ns, groups, wd);
-                    if (LIST == 1 && list_fits) keep_words(lwords, n_rec, wd);
-                    list_base(wd);
-                }
-                walk(ns, first, wd);
-            }
+            });
         }
         if (EXPORT) continue;
         // sum the slice partials of each home atom in slice order (red aliases the
@@ -382,77 +317,91 @@ __device__ __forceinline__ void force_cell(const SimArgs& a, int c, float4* tile
         }
         __syncthreads();
         const int k = home_first + h0 + h;
+        // the arguments of the epilogue, with this system's geometry
+        SimArgs l = late_args();
+        l.nc = a.nc;
+        l.cbase = a.cbase;
+        l.box = a.box;
+        l.inv_box = a.inv_box;
+        l.s = a.s;
+        l.inv_s = a.inv_s;
         int c_next = -1;  // DRIFT: the home atom's next cell, -1 on lanes without one
         float4 p_next = pi, v_next = make_float4(0.f, 0.f, 0.f, 0.f);
         if (lead) {
             if (LIST == 3) {  // the atom's list length (the entries past the capacity were not kept)
-                a.ncount[k] = min(lcount, a.nlist_cap);
-                if (lcount > a.nlist_cap) over = true;
+                l.ncount[k] = min(lcount, l.nlist_cap);
+                if (lcount > l.nlist_cap) over = true;
             }
             float gx = 0.f, gy = 0.f, gz = 0.f, gu = 0.f, gw = 0.f;
             for (int w = 0; w < nw; ++w) {
-                const float* part = red + 5 * kWave * w;
-                for (int q = 0; q < ns; ++q) {
-                    const int l = h + q * hstride;
-                    gx += part[0 * kWave + l];
-                    gy += part[1 * kWave + l];
-                    gz += part[2 * kWave + l];
+                const float* part = red + 5 * kWave * w + h;
+                auto add = [&](const float* p) {
+                    gx += p[0 * kWave];
+                    gy += p[1 * kWave];
+                    gz += p[2 * kWave];
                     if (ENERGY) {
-                        gu += part[3 * kWave + l];
-                        gw += part[4 * kWave + l];
+                        gu += p[3 * kWave];
+                        gw += p[4 * kWave];
                     }
+                };
+                if (ns == 4) {  // uniform: offsets are immediates, all reads in flight
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) add(part + q * 16);
+                } else {
+                    for (int q = 0; q < ns; ++q) add(part + q * hstride);
                 }
             }
             if (!finite3(gx, gy, gz)) bad = true;
-            if (WRITE) a.force[k] = make_float4(gx, gy, gz, 0.f);
+            if (WRITE) l.force[k] = make_float4(gx, gy, gz, 0.f);
             if (KICK || ENERGY) {
                 float4 v = vel;
                 if (KICK) {
-                    v.x += a.hdt_m * gx;
-                    v.y += a.hdt_m * gy;
-                    v.z += a.hdt_m * gz;
-                    if (!DRIFT) a.vel0[k] = v;
+                    v.x += l.hdt_m * gx;
+                    v.y += l.hdt_m * gy;
+                    v.z += l.hdt_m * gz;
+                    if (!DRIFT) l.vel0[k] = v;
                 }
                 if (ENERGY) {
                     u_acc += static_cast<double>(gu);
                     w_acc += static_cast<double>(gw);
-                    k_acc += static_cast<double>(a.half_m) * (static_cast<double>(v.x) * v.x +
+                    k_acc += static_cast<double>(l.half_m) * (static_cast<double>(v.x) * v.x +
                                                               static_cast<double>(v.y) * v.y +
                                                               static_cast<double>(v.z) * v.z);
                 }
                 if (DRIFT) {
                     v_next = v;
                     if (SKIN) {
-                        half_kick_drift_unwrapped(a, p_next, v_next, gx, gy, gz);
-                        a.pos2[k] = p_next;
-                        a.vel2[k] = v_next;
+                        half_kick_drift_unwrapped(l, p_next, v_next, gx, gy, gz);
+                        l.pos2[k] = p_next;
+                        l.vel2[k] = v_next;
                         if (LIST != 0) {
                             const float ex = p_next.x - pref.x, ey = p_next.y - pref.y, ez = p_next.z - pref.z;
-                            if (ex * ex + ey * ey + ez * ez > a.disp_half * a.disp_half) skin_out = true;
+                            if (ex * ex + ey * ey + ez * ez > l.disp_half * l.disp_half) skin_out = true;
                         } else {
-                            const float ex = fmaxf(fmaxf(ox - p_next.x, p_next.x - (ox + a.s)), 0.f);
-                            const float ey = fmaxf(fmaxf(oy - p_next.y, p_next.y - (oy + a.s)), 0.f);
-                            const float ez = fmaxf(fmaxf(oz - p_next.z, p_next.z - (oz + a.s)), 0.f);
-                            if (ex * ex + ey * ey + ez * ez > a.skin_half * a.skin_half) skin_out = true;
+                            const float ex = fmaxf(fmaxf(ox - p_next.x, p_next.x - (ox + l.s)), 0.f);
+                            const float ey = fmaxf(fmaxf(oy - p_next.y, p_next.y - (oy + l.s)), 0.f);
+                            const float ez = fmaxf(fmaxf(oz - p_next.z, p_next.z - (oz + l.s)), 0.f);
+                            if (ex * ex + ey * ey + ez * ez > l.skin_half * l.skin_half) skin_out = true;
                         }
                     } else {
-                        c_next = half_kick_drift(a, p_next, v_next, gx, gy, gz);
+                        c_next = half_kick_drift(l, p_next, v_next, gx, gy, gz);
                     }
                 }
             }
         }
-        if (DRIFT && !SKIN && wv == 0) bin_atom(a, p_next, v_next, c_next);  // all lanes of wavefront 0
+        if (DRIFT && !SKIN && wv == 0) bin_atom(l, p_next, v_next, c_next);  // all lanes of wavefront 0
     }
-    if (LIST == 1) a.plist_n[lrow] = list_fits ? n_rec : kListSpans + 1;  // kept words of several passes are not used
-    if ((EXPORT || LIST == 3) && over) atomicOr(&a.hdr[HDR_ERROR], DEV_NB_OVERFLOW);
-    if (bad) atomicOr(&a.hdr[HDR_ERROR], DEV_NONFINITE);
-    if (SKIN && skin_out) atomicOr(&a.hdr[HDR_ERROR], DEV_SKIN);
+    const SimArgs l = late_args();
+    if (LIST == 1) l.plist_n[lrow] = list_fits ? n_rec : kListSpans + 1;  // kept words of several passes are not used
+    if ((EXPORT || LIST == 3) && over) atomicOr(&l.hdr[HDR_ERROR], DEV_NB_OVERFLOW);
+    if (bad) atomicOr(&l.hdr[HDR_ERROR], DEV_NONFINITE);
+    if (SKIN && skin_out) atomicOr(&l.hdr[HDR_ERROR], DEV_SKIN);
     if (ENERGY) {
         u_acc = wave_sum(u_acc);
         w_acc = wave_sum(w_acc);
         k_acc = wave_sum(k_acc);
         if (threadIdx.x == 0) {
-            double* e = a.epart + 3 * static_cast<size_t>(a.cbase + c);
+            double* e = l.epart + 3 * static_cast<size_t>(a.cbase + c);
             e[0] = u_acc;
             e[1] = w_acc;
             e[2] = k_acc;
@@ -463,7 +412,7 @@ __device__ __forceinline__ void force_cell(const SimArgs& a, int c, float4* tile
 template <bool KICK, bool ENERGY, bool WRITE, bool DRIFT, int MW>
 __global__ void __launch_bounds__(MW * kWave) k_forces(SimArgs a, bool from_step) {
     if (from_step) {
-        if (a.hdr[HDR_ERROR] & DEV_ORDER) return;
+        if (scalar_load(a.hdr + HDR_ERROR) & DEV_ORDER) return;
     } else if (!state_ok(a, false)) {
         if (blockIdx.x == 0 && threadIdx.x == 0) atomicOr(&a.hdr[HDR_ERROR], DEV_ORDER);
         return;
@@ -480,7 +429,7 @@ __global__ void __launch_bounds__(MW * kWave) k_forces(SimArgs a, bool from_step
 // half kick and drift into pos2/vel2.
 template <bool ENERGY, int MW>
 __global__ void __launch_bounds__(MW * kWave) k_forces_skin(SimArgs a) {
-    if (a.hdr[HDR_ERROR] & DEV_ORDER) return;
+    if (scalar_load(a.hdr + HDR_ERROR) & DEV_ORDER) return;
     extern __shared__ float4 tile[];
     __shared__ Neighbourhood nb;
     force_cell<true, ENERGY, false, true, true, 0, false, MW>(a, xcd_block_order(blockIdx.x, a.ncells), tile, nb,
@@ -491,7 +440,7 @@ __global__ void __launch_bounds__(MW * kWave) k_forces_skin(SimArgs a) {
 // BIN: the drift bins for the next rebuild, else it goes to pos2/vel2.
 template <bool ENERGY, bool RECORD, bool BIN>
 __global__ void __launch_bounds__(kWave) k_forces_list(SimArgs a) {
-    if (a.hdr[HDR_ERROR] & DEV_ORDER) return;
+    if (scalar_load(a.hdr + HDR_ERROR) & DEV_ORDER) return;
     extern __shared__ float4 tile[];
     __shared__ Neighbourhood nb;
     force_cell<true, ENERGY, false, true, !BIN, RECORD ? 1 : 2>(a, xcd_block_order(blockIdx.x, a.ncells), tile, nb,
@@ -502,7 +451,7 @@ __global__ void __launch_bounds__(kWave) k_forces_list(SimArgs a) {
 // k_forces_list, and every atom's neighbour list within the list radius.
 template <bool ENERGY, bool BIN>
 __global__ void __launch_bounds__(kWave) k_forces_record(SimArgs a) {
-    if (a.hdr[HDR_ERROR] & DEV_ORDER) return;
+    if (scalar_load(a.hdr + HDR_ERROR) & DEV_ORDER) return;
     extern __shared__ float4 tile[];  // a.tile_cap + kTilePad positions, then as many 4-byte list entries
     __shared__ Neighbourhood nb;
     force_cell<true, ENERGY, false, true, !BIN, 3>(a, xcd_block_order(blockIdx.x, a.ncells), tile, nb,

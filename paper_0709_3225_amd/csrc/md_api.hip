@@ -181,6 +181,22 @@ bool aligned16(const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15) == 
 // wide margin, so the screen never drops a pair that the exact test accepts.
 float screen_bound(double rc, double s) { return static_cast<float>(rc * rc + std::ldexp(12.0 * s * s, -17)); }
 
+// Bound of the 16-bit screen, in units of the cell side s: (r / s)^2 plus a
+// margin above what rounding to 16 bits (half a unit of 2^-10 relative) can
+// take off a pair with r_ij <= r <= s. With home coordinates in [-d, 1 + d]
+// (atoms may leave their cell by d = (s - r_c) / 2 between rebuilds), centred
+// candidate coordinates |u| <= 1.5 + 2 d and |x_j|^2 <= (sqrt(3) (1 + d) + 1)^2:
+//   sum |u| err(2 v) + sum |2 v| err(u) + err(|x_j|^2)
+//   <= 3 (1.5 + 2 d) 2^-10 + 3 (2 + 2 d) 2^-11 + 2^-9 < 0.0095 for d < 0.05,
+//   <= 3 x 2 x 2^-10 + 3 x 2.5 x 2^-11 + 2^-8       < 0.0136 for d < 0.25
+// (d is below 0.25 only while s < 2 r_c; wider cells, up to d = 0.5: |u| < 2.5
+// and |x_j|^2 < 13, below 0.0250).
+float screen16_bound(double rc, double r, double s) {
+    const double d = 0.5 * (s - rc) / s;
+    const double margin = d < 0.05 ? 0.0100 : (d < 0.25 ? 0.0145 : 0.0260);
+    return static_cast<float>(r * r / (s * s) + margin);
+}
+
 // One LDS pass of the cell-pair kernels holds the mean 27-cell neighbourhood
 // plus 10% and half a wavefront (a liquid's neighbourhood counts vary by a few
 // percent; a larger one takes a second pass). A small tile leaves room for
@@ -194,6 +210,12 @@ int tile_capacity(int n, int ncells) {
 // Wavefronts per force workgroup: the caller's choice, else one (which is
 // as fast or faster from about 2,000 cells up).
 int waves_per_cell(const md_params* p) { return p->waves_per_cell != 0 ? p->waves_per_cell : 1; }
+
+// ceil(2^32 / nc): the kernels divide cell indices by nc through it (unused
+// for a batch's shared arguments, whose nc marks the batch).
+uint32_t division_magic(int nc) {
+    return nc < 2 ? 0u : static_cast<uint32_t>(((uint64_t{1} << 32) + static_cast<uint64_t>(nc) - 1) / static_cast<uint64_t>(nc));
+}
 
 SimArgs make_args(const md_params* p, const Layout& L, void* ws) {
     char* b = static_cast<char*>(ws);
@@ -234,6 +256,8 @@ SimArgs make_args(const md_params* p, const Layout& L, void* ws) {
     a.box = p->box;
     a.s = L.s;
     a.inv_s = L.inv_s;
+    a.inv_box = 1.0f / p->box;
+    a.nc_magic = division_magic(L.nc);
     // Pair constants: computed in double, rounded once.
     const double eps = p->epsilon, sig = p->sigma;
     const double rc = static_cast<double>(cutoff(p));
@@ -253,6 +277,7 @@ SimArgs make_args(const md_params* p, const Layout& L, void* ws) {
     a.fc = p->shift_mode == 0 ? static_cast<float>(flj_rc) : 0.f;
     a.uc = static_cast<float>(ulj_rc);
     a.screen2 = screen_bound(rc, L.s);
+    a.screen16 = screen16_bound(rc, rc, L.s);
     // half the margin of the cell side over r_c, less a relative 2^-20 for the
     // FP32 comparison
     a.skin_half = static_cast<float>(std::max(0.0, 0.5 * (static_cast<double>(L.s) - rc) * (1.0 - std::ldexp(1.0, -20))));
@@ -262,6 +287,7 @@ SimArgs make_args(const md_params* p, const Layout& L, void* ws) {
     // while no atom has moved by half of r_V - r_c (less a relative 2^-20)
     const double rv = p->list_radius > 0.f ? static_cast<double>(p->list_radius) : static_cast<double>(L.s);
     a.list_screen2 = screen_bound(rv, L.s);
+    a.list_screen16 = screen16_bound(rc, rv, L.s);
     a.disp_half = static_cast<float>(std::max(0.0, 0.5 * (rv - rc) * (1.0 - std::ldexp(1.0, -20))));
     a.tile_cap = p->tile_cap != 0 ? p->tile_cap : tile_capacity(p->n, L.ncells);
     a.waves = waves_per_cell(p);
@@ -522,7 +548,10 @@ md_status batch_plan(const md_params* p, const md_replica* reps, int32_t count, 
         r.box = q.box;
         r.s = Lb.s;
         r.inv_s = Lb.inv_s;
+        r.inv_box = 1.0f / q.box;
+        r.nc_magic = division_magic(Lb.nc);
         r.screen2 = screen_bound(static_cast<double>(cutoff(&q)), Lb.s);
+        r.screen16 = screen16_bound(static_cast<double>(cutoff(&q)), static_cast<double>(cutoff(&q)), Lb.s);
         B.max_mean = std::max(B.max_mean, static_cast<double>(q.n) / Lb.ncells);
         ntot += q.n;
         ctot += Lb.ncells;

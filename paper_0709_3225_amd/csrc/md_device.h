@@ -12,6 +12,15 @@ namespace mdlj {
 
 constexpr int kWave = 64;
 
+// The lane number, opaque at this point: what is computed from it stays here.
+// (The compiler moves lane-only values in front of the cell passes' loops,
+// which mostly run once; held across the pair walk they cost 20 registers.)
+__device__ __forceinline__ int lane_here() {
+    int l = __lane_id();
+    asm volatile("" : "+v"(l));
+    return l;
+}
+
 // Bring one FP32 coordinate into [0, L). x - L*floor(x/L) can round to L
 // exactly; then subtract L once more, and fall back to 0 for the last ulp.
 __device__ __forceinline__ float wrap_coord(float x, float L, float invL) {
@@ -22,12 +31,13 @@ __device__ __forceinline__ float wrap_coord(float x, float L, float invL) {
 }
 
 __device__ __forceinline__ int cell_coord(float x, float inv_s, int nc) {
-    int i = static_cast<int>(x * inv_s);
-    return i < 0 ? 0 : (i >= nc ? nc - 1 : i);
+    return max(0, min(static_cast<int>(x * inv_s), nc - 1));
 }
 
 __device__ __forceinline__ int cell_index(float x, float y, float z, const SimArgs& a) {
-    return cell_coord(x, a.inv_s, a.nc) + a.nc * (cell_coord(y, a.inv_s, a.nc) + a.nc * cell_coord(z, a.inv_s, a.nc));
+    // (nc^3 fits an int, so nc^2 and both products' factors fit 24 bits)
+    const uint32_t row = __umul24(cell_coord(z, a.inv_s, a.nc), a.nc) + cell_coord(y, a.inv_s, a.nc);
+    return static_cast<int>(__umul24(row, a.nc) + cell_coord(x, a.inv_s, a.nc));
 }
 
 __device__ __forceinline__ bool finite3(float x, float y, float z) {
@@ -55,7 +65,7 @@ __device__ __forceinline__ void half_kick_drift_unwrapped(const SimArgs& a, floa
 
 __device__ __forceinline__ int half_kick_drift(const SimArgs& a, float4& p, float4& v, float fx, float fy,
                                                float fz) {
-    const float invL = 1.0f / a.box;
+    const float invL = a.inv_box;
     half_kick_drift_unwrapped(a, p, v, fx, fy, fz);
     p.x = wrap_coord(p.x, a.box, invL);
     p.y = wrap_coord(p.y, a.box, invL);
@@ -72,8 +82,8 @@ __device__ __forceinline__ int half_kick_drift(const SimArgs& a, float4& p, floa
 // serialise (about 0.15 us each here), so nothing coarser than 16 cells is
 // counted atomically. Must be called by all 64 lanes of the wave.
 __device__ __forceinline__ int histogram_rank(int* count, int* bcount, int c) {
-    const int lane = __lane_id();
-    const int prev = __shfl_up(c, 1);
+    const int lane = lane_here();
+    const int prev = __builtin_amdgcn_update_dpp(c, c, 0x138, 0xf, 0xf, false);  // wave_shr:1
     const bool head = (lane == 0) || (prev != c);
     const uint64_t heads = __ballot(head);
     const uint64_t upto = (lane == 63) ? ~0ull : ((2ull << lane) - 1ull);
@@ -86,14 +96,14 @@ __device__ __forceinline__ int histogram_rank(int* count, int* bcount, int c) {
         // the block counts, one atomic per run of lanes in the same block of
         // cells (several cells of a run share a block counter)
         const int bk = c >= 0 ? (c >> kBlockShift) : -1;
-        const int prevb = __shfl_up(bk, 1);
+        const int prevb = __builtin_amdgcn_update_dpp(bk, bk, 0x138, 0xf, 0xf, false);
         const bool bhead = (lane == 0) || (prevb != bk);
         const uint64_t bheads = __ballot(bhead);
         const uint64_t babove = bheads & ~upto;
         const int next_bhead = babove ? (__ffsll(static_cast<unsigned long long>(babove)) - 1) : kWave;
         if (bhead && bk >= 0) atomicAdd(&bcount[bk], next_bhead - lane);
     }
-    base = __shfl(base, my_head);
+    base = __builtin_amdgcn_ds_bpermute(4 * my_head, base);
     return base + (lane - my_head);
 }
 
@@ -105,7 +115,8 @@ __device__ __forceinline__ void bin_atom(const SimArgs& a, float4 p, float4 v, i
     const int r = histogram_rank(a.counts, a.direct ? a.bcounts + a.par * a.nbstride : nullptr, c);
     if (c < 0) return;
     if (r < a.cap) {
-        const size_t e = static_cast<size_t>(c) * a.cap + r;
+        const uint64_t e = static_cast<uint64_t>(static_cast<uint32_t>(c)) * static_cast<uint32_t>(a.cap) +
+                           static_cast<uint32_t>(r);
         a.bpos[e] = p;
         a.bvel[e] = v;
     } else {
@@ -165,7 +176,23 @@ __device__ __forceinline__ SimArgs replica_view(const SimArgs& base, const Repli
     a.box = r.box;
     a.s = r.s;
     a.inv_s = r.inv_s;
+    a.inv_box = r.inv_box;
+    a.nc_magic = r.nc_magic;
     a.screen2 = r.screen2;
+    a.screen16 = r.screen16;
+    return a;
+}
+
+// The kernel's first argument, read again from the kernel argument segment at
+// this point: what only the end of a long kernel needs then takes no scalar
+// registers before it (kept from the start, the binning's arrays spilled
+// scalar registers of the cell passes, two vector instructions per spill).
+__device__ __forceinline__ SimArgs late_args() {
+    auto p = reinterpret_cast<const __attribute__((address_space(4))) SimArgs*>(
+        reinterpret_cast<uintptr_t>(__builtin_amdgcn_kernarg_segment_ptr()));
+    asm volatile("" : "+s"(p));
+    SimArgs a;
+    __builtin_memcpy(&a, p, sizeof(SimArgs));
     return a;
 }
 

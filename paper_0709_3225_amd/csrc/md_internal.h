@@ -67,6 +67,7 @@ struct SimArgs {
     uint32_t* nlist;
     int* ncount;
     int nlist_cap;
+    float list_screen16; // the same for the 16-bit screen, in units of the cell side
     float list_screen2;  // screen bound when the words are kept (cell side^2 plus the screen margin)
     float disp_half;     // largest displacement since recording: (side - r_c) / 2
     // Cell build: per-cell histogram, zero between builds; a binned atom's
@@ -97,6 +98,8 @@ struct SimArgs {
     float box;
     float s;         // cell side box / nc
     float inv_s;     // nc / box
+    float inv_box;   // 1 / box
+    uint32_t nc_magic;  // ceil(2^32 / nc)
 
     float rc2;       // r_c^2 (FP32)
     float rc;
@@ -108,6 +111,7 @@ struct SimArgs {
     float fc;        // f_LJ(r_c) for the force shift, 0 for energy shift
     float uc;        // u_LJ(r_c)
     float screen2;   // conservative bound on r^2 for the dot-product screen
+    float screen16;  // the same for the 16-bit screen, in units of the cell side
     int tile_cap;    // staged atoms per LDS pass of the force kernel
     int waves;       // wavefronts per force workgroup (1, 2 or 4), sharing one staged tile
 
@@ -120,7 +124,8 @@ struct SimArgs {
 // [cbase, cbase + ncells) of the batch's arrays; geometry as in SimArgs.
 struct Replica {
     int n, abase, nc, ncells, cbase, tile_cap;
-    float box, s, inv_s, screen2;
+    float box, s, inv_s, screen2, screen16, inv_box;
+    uint32_t nc_magic;
     int lbase;  // first entry of the replica's cells in the tile-class cell list
 };
 

@@ -213,6 +213,50 @@ def test_every_home_layout_matches_oracle(k, waves, orc):
     _assert_rows(counts, idx, counts_o, idx_o)
 
 
+def _k_per_cell_fine(k, seed, side, nc=4):
+    """k <= 64 atoms in every cell, on sites of a 4^3 sub-lattice (spacing side
+    / 4) with a jitter of +-0.03; drawn again until no pair is within 2e-5 of
+    r_c = 2.5."""
+    u = (np.arange(4) + 0.5) * side / 4
+    sites = np.stack(np.meshgrid(u, u, u, indexing="ij"), -1).reshape(-1, 3)
+    cells = np.stack(np.meshgrid(*(np.arange(nc),) * 3, indexing="ij"), -1).reshape(-1, 3) * side
+    for attempt in range(100):
+        rng = np.random.default_rng(seed + 1000 * attempt)
+        pts = np.concatenate([c + sites[rng.choice(64, size=k, replace=False)] for c in cells])
+        pos4 = np.zeros((len(pts), 4), np.float32)
+        pos4[:, :3] = pts + rng.uniform(-0.03, 0.03, pts.shape)
+        x = pos4[:, :3].astype(np.float64)
+        d = x[:, None] - x[None]
+        d -= nc * side * np.round(d / (nc * side))
+        if not (np.abs(np.sqrt((d * d).sum(-1)) - 2.5) < 2e-5).any():
+            return pos4, nc * side
+    raise ValueError("no instance clear of r_c")
+
+
+@pytest.mark.parametrize("k,waves,side", [(11, 2, 2.51), (16, 4, 2.51), (17, 2, 2.51), (21, 2, 3.25), (22, 2, 2.51),
+                                          (25, 1, 2.51), (31, 1, 3.25), (32, 1, 2.51), (32, 2, 4.9), (32, 4, 3.25),
+                                          (33, 1, 2.51), (14, 1, 4.9), (19, 4, 4.9)])
+def test_matrix_screen_edges_match_oracle(k, waves, side, orc):
+    """The 16-bit matrix-core screen at the edges of its layouts (16 | 17,
+    21 | 22, 32 | 33 atoms), with wavefronts sharing a cell, and for sides that
+    fall under each of its three margins (s close to r_c, s = 1.3 r_c, s just
+    below 2 r_c). It may only ever accept more than the exact test: a dropped
+    pair would move a force by |f_LJ(r_c)| (plain truncated force), the sets of
+    accepted pairs are the oracle's."""
+    pos4, box = _k_per_cell_fine(k, 300 + k, side)
+    _say(f"matrix screen k={k} waves={waves} side={side}")
+    p = orc.params(box, shift_mode=1)
+    counts_o, idx_o, guard = orc.neighbors(p, pos4)
+    assert guard == 0, "instance has pairs within the FP32/FP64 guard band of r_c"
+    s, f, _ = gpu_forces(pos4, box, shift_mode=1, waves_per_cell=waves, cell_min=0.999 * side)
+    assert s.cells_per_dim == 4
+    fo, _, _ = orc.forces(p, pos4)
+    assert rel_l2(f, fo) <= FORCE_TOL
+    counts, idx = s.neighbors(int(counts_o.max()) + 8)
+    assert s.check() == 0
+    _assert_rows(counts, idx, counts_o, idx_o)
+
+
 @pytest.mark.parametrize("case", ["lj4k_jitter_shuffled", "lj32k_jitter", "fcc_rho1.2_jitter", "dense_clump",
                                   "cells_of_5", "cells_of_18", "cells_of_22"])
 def test_neighbor_sets_pair_lists(case, orc):
