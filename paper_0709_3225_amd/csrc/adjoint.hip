@@ -277,9 +277,8 @@ constexpr int kThetaBlock = 1024;
 constexpr int kThetaUnroll = 8;
 __global__ void __launch_bounds__(kThetaBlock) k_theta_final(SimArgs a, double* theta, double coef) {
     if (!state_ok(a, false)) return;
-    __shared__ double s0[kThetaBlock], s1[kThetaBlock];
     const int t = threadIdx.x;
-    double x0 = 0.0, x1 = 0.0;
+    double x[2] = {0.0, 0.0};
     for (int b0 = t; b0 < a.ncells; b0 += kThetaBlock * kThetaUnroll) {
         double p0[kThetaUnroll], p1[kThetaUnroll];
 #pragma unroll
@@ -291,24 +290,15 @@ __global__ void __launch_bounds__(kThetaBlock) k_theta_final(SimArgs a, double* 
 #pragma unroll
         for (int q = 0; q < kThetaUnroll; ++q) {
             if (b0 + q * kThetaBlock < a.ncells) {
-                x0 += p0[q];
-                x1 += p1[q];
+                x[0] += p0[q];
+                x[1] += p1[q];
             }
         }
     }
-    s0[t] = x0;
-    s1[t] = x1;
-    __syncthreads();
-    for (int off = kThetaBlock / 2; off > 0; off >>= 1) {
-        if (t < off) {
-            s0[t] += s0[t + off];
-            s1[t] += s1[t + off];
-        }
-        __syncthreads();
-    }
+    block_sum<kThetaBlock>(x, t);
     if (t == 0) {
-        theta[0] += coef * s0[0];
-        theta[1] += coef * s1[0];
+        theta[0] += coef * x[0];
+        theta[1] += coef * x[1];
     }
 }
 

@@ -2,15 +2,19 @@
 // side >= r_c; section 3.1 membership kept current as particles move), and the
 // velocity-Verlet drift that feeds it (section 2).
 //
-// A build is three launches:
+// A build is two or three launches, four when a state is loaded on a small
+// grid:
 //   bin        : wrap + cell index + histogram rank (one atomic per run of
 //                equal cells in a wavefront); the atom's position and
 //                velocity go to its cell's bucket (or the overflow list
 //                beyond the bucket capacity).
 //                Inside a multi-step run the force kernel's epilogue bins the
 //                drifted atoms, so this launch only starts a build or a run.
-//   block scan : one workgroup sums the histogram over blocks of 16 cells
-//                and scans the sums into the atoms before each block.
+//   block count: grids of at most kDirectBlocks blocks whose atoms came in the
+//                caller's order: the histogram summed over blocks of 16 cells.
+//                Atoms binned in cell order count their blocks as they go.
+//   block scan : larger grids: the histogram summed over blocks of 16 cells
+//                and the sums scanned into the atoms before each block.
 //   cell order : the workgroup of a 16-cell block adds its cells' counts to
 //                the block's offset, writes the cell offsets, clears its
 //                cells' counts, orders each cell's members by user index and
@@ -49,14 +53,32 @@ __global__ void k_set_state(SimArgs a, int state) {
     if (blockIdx.x == 0 && threadIdx.x == 0) a.hdr[HDR_STATE] = state;
 }
 
-// Clear the counters of parity par (overflow count, block histogram).
-__global__ void __launch_bounds__(kBlock) k_zero_blocks(SimArgs a, int par) {
+// Clear the counters of parity 0 (overflow count, block histogram).
+__global__ void __launch_bounds__(kBlock) k_zero_blocks(SimArgs a) {
     const int t = blockIdx.x * kBlock + threadIdx.x;
     if (t == 0) {
-        a.hdr[HDR_OVF + par] = 0;
-        a.hdr[HDR_OVFA + par] = 0;
+        a.hdr[HDR_OVF] = 0;
+        a.hdr[HDR_OVFA] = 0;
     }
-    for (int b = t; b < a.nbstride; b += gridDim.x * kBlock) a.bcounts[par * a.nbstride + b] = 0;
+    for (int b = t; b < a.nbstride; b += gridDim.x * kBlock) a.bcounts[b] = 0;
+}
+
+// Block histogram (parity par) of a loaded state from its cells' counts. Atoms
+// in the caller's order would count their blocks one atomic each, several
+// hundred on every counter: the load then took 20.6 us at N = 32,000 and 26.2 us
+// at N = 100,003; without them 4.9 and 5.5 us, and this launch 1.6 us.
+__global__ void __launch_bounds__(kBlock) k_block_counts(SimArgs a) {
+    const int b = blockIdx.x * kBlock + threadIdx.x;
+    if (b >= a.nblocks) return;
+    // counts holds whole blocks (zero past the last cell)
+    const int4* c = reinterpret_cast<const int4*>(a.counts) + b * ((1 << kBlockShift) / 4);
+    int t = 0;
+#pragma unroll
+    for (int q = 0; q < (1 << kBlockShift) / 4; ++q) {
+        const int4 x = c[q];
+        t += x.x + x.y + x.z + x.w;
+    }
+    a.bcounts[a.par * a.nbstride + b] = t;
 }
 
 // Load one user-order atom i: wrap, cell index, binning.
@@ -81,7 +103,7 @@ __device__ __forceinline__ void load_atom(const SimArgs& a, int i, bool valid, c
         v.w = 0.f;
         c = a.cbase + cell_index(p.x, p.y, p.z, a);
     }
-    bin_atom(a, p, v, c);
+    bin_atom<false>(a, p, v, c);
 }
 
 // Velocity-Verlet first half for sorted slot i (half kick, drift, wrap), then
@@ -475,7 +497,15 @@ hipError_t launch_build_init(const SimArgs& a, hipStream_t st) {
 }
 
 hipError_t launch_load(const SimArgs& a, const float4* pos_in, const float4* vel_in, hipStream_t st) {
-    hipLaunchKernelGGL(k_load, dim3(blocks_for(a.n, kBlock)), dim3(kBlock), 0, st, with_par(a, 0), pos_in, vel_in);
+    hipLaunchKernelGGL(k_load, dim3(blocks_for(a.n, kBlock)), dim3(kBlock), 0, st, with_par(a, kLoadPar), pos_in,
+                       vel_in);
+    return launch_block_counts(a, st);
+}
+
+hipError_t launch_block_counts(const SimArgs& a, hipStream_t st) {
+    if (a.direct)
+        hipLaunchKernelGGL(k_block_counts, dim3(blocks_for(a.nblocks, kBlock)), dim3(kBlock), 0, st,
+                           with_par(a, kLoadPar));
     return hipGetLastError();
 }
 
@@ -501,9 +531,9 @@ hipError_t launch_set_state(const SimArgs& a, int state, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_zero_blocks(const SimArgs& a, int par, hipStream_t st) {
-    hipLaunchKernelGGL(k_zero_blocks, dim3(clamp_blocks(blocks_for(a.nbstride, kBlock))), dim3(kBlock), 0, st, a,
-                       par);
+hipError_t launch_end_builds(const SimArgs& a, int par, hipStream_t st) {
+    if (par == 0)
+        hipLaunchKernelGGL(k_zero_blocks, dim3(clamp_blocks(blocks_for(a.nbstride, kBlock))), dim3(kBlock), 0, st, a);
     return hipGetLastError();
 }
 
@@ -523,9 +553,9 @@ hipError_t launch_batch_setup(const SimArgs& base, const Replica* reps, int* ato
 
 hipError_t launch_batch_load(const SimArgs& base, const Replica* reps, const int* atom_rep, const float4* pos_in,
                              const float4* vel_in, hipStream_t st) {
-    hipLaunchKernelGGL(k_batch_load, dim3(blocks_for(base.n, kBlock)), dim3(kBlock), 0, st, with_par(base, 0), reps,
-                       atom_rep, pos_in, vel_in);
-    return hipGetLastError();
+    hipLaunchKernelGGL(k_batch_load, dim3(blocks_for(base.n, kBlock)), dim3(kBlock), 0, st, with_par(base, kLoadPar),
+                       reps, atom_rep, pos_in, vel_in);
+    return launch_block_counts(base, st);
 }
 
 hipError_t launch_batch_integrate(const SimArgs& base, const Replica* reps, const int* atom_rep, hipStream_t st) {

@@ -648,32 +648,20 @@ template <bool LOSS>
 __global__ void __launch_bounds__(kFinalBlock) k_energy_final(SimArgs a, double* out3, bool from_step, double kcoef,
                                                               double wcoef) {
     if (from_step && (a.hdr[HDR_ERROR] & DEV_ORDER)) return;
-    __shared__ double su[kFinalBlock], sw[kFinalBlock], sk[kFinalBlock];
     const int t = threadIdx.x;
-    double u = 0.0, w = 0.0, k = 0.0;
-    sum_partials<kFinalBlock>(a.epart, a.ncells, t, u, w, k);
-    su[t] = u;
-    sw[t] = w;
-    sk[t] = k;
-    __syncthreads();
-    for (int off = kFinalBlock / 2; off > 0; off >>= 1) {
-        if (t < off) {
-            su[t] += su[t + off];
-            sw[t] += sw[t + off];
-            sk[t] += sk[t + off];
-        }
-        __syncthreads();
-    }
+    double x[3] = {0.0, 0.0, 0.0};
+    sum_partials<kFinalBlock>(a.epart, a.ncells, t, x[0], x[1], x[2]);
+    block_sum<kFinalBlock>(x, t);
     if (t == 0) {
         if (LOSS) {
-            out3[0] = kcoef * sk[0] + wcoef * (0.5 * sw[0]);
+            out3[0] = kcoef * x[2] + wcoef * (0.5 * x[1]);
         } else {
-            out3[0] = 0.5 * su[0];
-            out3[1] = sk[0];
-            out3[2] = 0.5 * sw[0];
+            out3[0] = 0.5 * x[0];
+            out3[1] = x[2];
+            out3[2] = 0.5 * x[1];
             if (wcoef != 0.0) {
-                out3[3] = kcoef * sk[0];
-                out3[4] = wcoef * (2.0 * sk[0] + 0.5 * sw[0]);
+                out3[3] = kcoef * x[2];
+                out3[4] = wcoef * (2.0 * x[2] + 0.5 * x[1]);
             }
         }
     }
@@ -684,27 +672,15 @@ __global__ void __launch_bounds__(kFinalBlock) k_energy_final(SimArgs a, double*
 __global__ void __launch_bounds__(kRedBlock)
     k_batch_energy_final(SimArgs base, const Replica* __restrict__ reps, double* out) {
     if (base.hdr[HDR_ERROR] & DEV_ORDER) return;
-    __shared__ double su[kRedBlock], sw[kRedBlock], sk[kRedBlock];
     const Replica r = reps[blockIdx.x];
     const int t = threadIdx.x;
-    double u = 0.0, w = 0.0, k = 0.0;
-    sum_partials<kRedBlock>(base.epart + 3 * static_cast<size_t>(r.cbase), r.ncells, t, u, w, k);
-    su[t] = u;
-    sw[t] = w;
-    sk[t] = k;
-    __syncthreads();
-    for (int off = kRedBlock / 2; off > 0; off >>= 1) {
-        if (t < off) {
-            su[t] += su[t + off];
-            sw[t] += sw[t + off];
-            sk[t] += sk[t + off];
-        }
-        __syncthreads();
-    }
+    double x[3] = {0.0, 0.0, 0.0};
+    sum_partials<kRedBlock>(base.epart + 3 * static_cast<size_t>(r.cbase), r.ncells, t, x[0], x[1], x[2]);
+    block_sum<kRedBlock>(x, t);
     if (t == 0) {
-        out[3 * blockIdx.x + 0] = 0.5 * su[0];
-        out[3 * blockIdx.x + 1] = sk[0];
-        out[3 * blockIdx.x + 2] = 0.5 * sw[0];
+        out[3 * blockIdx.x + 0] = 0.5 * x[0];
+        out[3 * blockIdx.x + 1] = x[2];
+        out[3 * blockIdx.x + 2] = 0.5 * x[1];
     }
 }
 

@@ -314,7 +314,12 @@ void loss_coefficients(const md_params* p, double scale, double& kc, double& wc)
 
 
 
-// Cell offsets and sorted arrays from the binned atoms (block histogram par).
+// Cell offsets and sorted arrays from the binned atoms (counters of parity
+// par). Between calls the counters of parity 0 are zero: a build clears the
+// other parity's, so a call whose last build has parity 1 leaves them so, and
+// one that ends on parity 0 clears them (launch_end_builds). Parity 1 is cleared
+// by the first build of parity 0, before anything bins into it; a load builds
+// with parity 1 on counters that are all zero.
 md_status rebuild(const SimArgs& a, int par, bool from_step, hipStream_t st) {
     if (!a.direct) MD_TRY_HIP(launch_block_scan(a, from_step, st), "block scan");
     MD_TRY_HIP(launch_cell_order(a, par, from_step, st), "cell order");
@@ -325,10 +330,7 @@ md_status rebuild(const SimArgs& a, int par, bool from_step, hipStream_t st) {
 md_status build_cells_impl(const SimArgs& a, const float4* pos4, const float4* vel4, hipStream_t stream) {
     MD_TRY_HIP(launch_build_init(a, stream), "build init");
     MD_TRY_HIP(launch_load(a, pos4, vel4, stream), "load");
-    md_status s = rebuild(a, 0, false, stream);
-    if (s != MD_OK) return s;
-    MD_TRY_HIP(launch_zero_blocks(a, 0, stream), "counter clear");
-    return MD_OK;
+    return rebuild(a, kLoadPar, false, stream);
 }
 
 // ---- a workspace that needs no allocation (md_forces_noalloc) ----------------
@@ -369,7 +371,7 @@ md_status steps_impl(const SimArgs& a, int32_t nsteps, int32_t thermo_every, dou
     // half kick, drift and binning, so the drift kernel runs only on the first
     // step; a rebuild is then the block scan (large grids) and the cell order.
     // Step k's atoms are binned with parity (k - 1) mod 2; the counters of
-    // both parities are zero again on return.
+    // parity 0 are zero again on return.
     for (int32_t k = 1; k <= nsteps; ++k) {
         const bool energy = thermo && thermo_every > 0 && (k % thermo_every) == 0;
         const bool last = k == nsteps;
@@ -381,7 +383,7 @@ md_status steps_impl(const SimArgs& a, int32_t nsteps, int32_t thermo_every, dou
             MD_TRY_HIP(launch_energy_final(a, thermo + 3 * static_cast<size_t>(k / thermo_every - 1), stream),
                        "energy");
     }
-    if (nsteps > 0) MD_TRY_HIP(launch_zero_blocks(a, (nsteps - 1) & 1, stream), "counter clear");
+    if (nsteps > 0) MD_TRY_HIP(launch_end_builds(a, (nsteps - 1) & 1, stream), "counter clear");
     return MD_OK;
 }
 
@@ -430,9 +432,8 @@ md_status recompute_impl(const SimArgs& a, const float* ckpt_pos4, const float* 
     MD_TRY_HIP(launch_load(a0, reinterpret_cast<const float4*>(ckpt_pos4), reinterpret_cast<const float4*>(ckpt_vel4),
                            stream),
                "load");
-    md_status s = rebuild(a0, 0, false, stream);
+    md_status s = rebuild(a0, kLoadPar, false, stream);
     if (s != MD_OK) return s;
-    MD_TRY_HIP(launch_zero_blocks(a0, 0, stream), "counter clear");
     if (nsteps > 1) {
         MD_TRY_HIP(launch_forces(a0, false, false, true, false, false, 0, stream), "forces");
         MD_TRY_HIP(launch_integrate(a0, stream), "integrate");
@@ -441,7 +442,7 @@ md_status recompute_impl(const SimArgs& a, const float* ckpt_pos4, const float* 
             if ((s = rebuild(ak, (k - 1) & 1, true, stream)) != MD_OK) return s;
             if (k + 1 < nsteps) MD_TRY_HIP(launch_forces(ak, true, false, false, true, true, k & 1, stream), "forces");
         }
-        MD_TRY_HIP(launch_zero_blocks(a, (nsteps - 2) & 1, stream), "counter clear");
+        MD_TRY_HIP(launch_end_builds(a, (nsteps - 2) & 1, stream), "counter clear");
     }
     return MD_OK;
 }
@@ -663,7 +664,7 @@ md_status batch_steps(const BatchPlan& B, const BatchArgs& ba, int32_t nsteps, i
                                                  thermo + 3 * static_cast<size_t>(B.count) * (k / thermo_every - 1), st),
                        "batch energy");
     }
-    if (nsteps > 0) MD_TRY_HIP(launch_zero_blocks(ba.base, (nsteps - 1) & 1, st), "batch counter clear");
+    if (nsteps > 0) MD_TRY_HIP(launch_end_builds(ba.base, (nsteps - 1) & 1, st), "batch counter clear");
     return MD_OK;
 }
 
@@ -793,7 +794,7 @@ md_status md_step_every(const md_params* p, void* ws, size_t ws_bytes, int32_t n
             MD_TRY_HIP(launch_energy_final(a, thermo + 3 * static_cast<size_t>(k / thermo_every - 1), stream),
                        "energy");
     }
-    if (nsteps > 0) MD_TRY_HIP(launch_zero_blocks(a, b & 1, stream), "counter clear");
+    if (nsteps > 0) MD_TRY_HIP(launch_end_builds(a, b & 1, stream), "counter clear");
     return MD_OK;
 }
 
@@ -840,7 +841,7 @@ md_status md_step_list(const md_params* p, void* ws, size_t ws_bytes, int32_t ns
             MD_TRY_HIP(launch_energy_final(a, thermo + 3 * static_cast<size_t>(k / thermo_every - 1), stream),
                        "energy");
     }
-    if (nsteps > 0) MD_TRY_HIP(launch_zero_blocks(a, b & 1, stream), "counter clear");
+    if (nsteps > 0) MD_TRY_HIP(launch_end_builds(a, b & 1, stream), "counter clear");
     return MD_OK;
 }
 
@@ -900,7 +901,7 @@ md_status md_step_nlist(const md_params* p, void* ws, size_t ws_bytes, int32_t n
             MD_TRY_HIP(launch_energy_final(a, thermo + 3 * static_cast<size_t>(k / thermo_every - 1), stream),
                        "energy");
     }
-    if (nsteps > 0) MD_TRY_HIP(launch_zero_blocks(a, b & 1, stream), "counter clear");
+    if (nsteps > 0) MD_TRY_HIP(launch_end_builds(a, b & 1, stream), "counter clear");
     return MD_OK;
 }
 
@@ -1089,7 +1090,7 @@ md_status md_step_path(const md_params* p, void* ws, size_t ws_bytes, int32_t ns
         if ((s = rebuild(ak, (k - 1) & 1, true, stream)) != MD_OK) return s;
         MD_TRY_HIP(launch_forces(ak, true, false, last, true, !last, k & 1, stream), "forces");
     }
-    MD_TRY_HIP(launch_zero_blocks(a, (nsteps - 1) & 1, stream), "counter clear");
+    MD_TRY_HIP(launch_end_builds(a, (nsteps - 1) & 1, stream), "counter clear");
     return MD_OK;
 }
 
@@ -1174,9 +1175,7 @@ md_status md_batch_build(const md_params* p, const md_replica* reps, int32_t cou
     MD_TRY_HIP(launch_batch_load(ba.base, ba.reps, ba.atom_rep, reinterpret_cast<const float4*>(pos4),
                                  reinterpret_cast<const float4*>(vel4), stream),
                "batch load");
-    if ((s = rebuild(ba.base, 0, false, stream)) != MD_OK) return s;
-    MD_TRY_HIP(launch_zero_blocks(ba.base, 0, stream), "batch counter clear");
-    return MD_OK;
+    return rebuild(ba.base, kLoadPar, false, stream);
 }
 
 md_status md_batch_forces(const md_params* p, const md_replica* reps, int32_t count, void* ws, size_t ws_bytes,

@@ -111,8 +111,10 @@ __device__ __forceinline__ int histogram_rank(int* count, int* bcount, int c) {
 // (global index; c < 0: this lane has no atom): rank in the cell, then the
 // atom goes to the cell's bucket, or to the overflow list once the bucket is
 // full. Must be called by all 64 lanes of the wave.
+// BLOCKS: on a direct grid the block histogram is counted too.
+template <bool BLOCKS = true>
 __device__ __forceinline__ void bin_atom(const SimArgs& a, float4 p, float4 v, int c) {
-    const int r = histogram_rank(a.counts, a.direct ? a.bcounts + a.par * a.nbstride : nullptr, c);
+    const int r = histogram_rank(a.counts, BLOCKS && a.direct ? a.bcounts + a.par * a.nbstride : nullptr, c);
     if (c < 0) return;
     if (r < a.cap) {
         const uint64_t e = static_cast<uint64_t>(static_cast<uint32_t>(c)) * static_cast<uint32_t>(a.cap) +
@@ -142,6 +144,32 @@ __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
     return v;
+}
+
+// Sums over a workgroup of BLOCK lanes as a binary tree (lane t takes t + BLOCK
+// / 2, then t + BLOCK / 4, ...); the results are in lane 0. The first wavefront
+// does the tree's levels above 64 on what all lanes stored and the others by
+// shuffles: one barrier, where a tree level at a time took ten and 1 us of the
+// single-workgroup sums.
+template <int BLOCK, int K>
+__device__ __forceinline__ void block_sum(double (&x)[K], int t) {
+    constexpr int kWaves = BLOCK / kWave;
+    __shared__ double part[K][BLOCK];
+#pragma unroll
+    for (int q = 0; q < K; ++q) part[q][t] = x[q];
+    __syncthreads();
+    if (t >= kWave) return;
+#pragma unroll
+    for (int q = 0; q < K; ++q) {
+        double v[kWaves];
+#pragma unroll
+        for (int j = 0; j < kWaves; ++j) v[j] = part[q][j * kWave + t];
+#pragma unroll
+        for (int off = kWaves / 2; off > 0; off >>= 1)
+#pragma unroll
+            for (int j = 0; j < off; ++j) v[j] += v[j + off];
+        x[q] = wave_sum(v[0]);
+    }
 }
 
 __device__ __forceinline__ int wave_incl_scan(int v) {

@@ -26,6 +26,7 @@ enum : int { STATE_BUILDING = 0x4D440000, STATE_CELLS = 0x4D440001, STATE_FORCES
 // kDirectBlocks blocks each workgroup sums the block counts before its own.
 constexpr int kBlockShift = 4;
 constexpr int kDirectBlocks = 2048;
+constexpr int kLoadPar = 1;  // counters a load's build uses
 // Pair lists: a cell's lanes keep the accept words of its screen (one span
 // covers 128 candidates of a lane; a liquid-density neighbourhood of about
 // 400 atoms needs one span with four slices, two with two or three).
@@ -149,7 +150,9 @@ hipError_t launch_load(const SimArgs& a, const float4* pos_in, const float4* vel
 // one given to launch_forces.
 hipError_t launch_block_scan(const SimArgs& a, bool from_step, hipStream_t st);
 hipError_t launch_cell_order(const SimArgs& a, int par, bool from_step, hipStream_t st);
-hipError_t launch_zero_blocks(const SimArgs& a, int par, hipStream_t st);
+hipError_t launch_block_counts(const SimArgs& a, hipStream_t st);
+// After the last build of a call (parity par): the counters of parity 0 are zero.
+hipError_t launch_end_builds(const SimArgs& a, int par, hipStream_t st);
 hipError_t launch_integrate(const SimArgs& a, hipStream_t st);
 hipError_t launch_forces(const SimArgs& a, bool kick, bool energy, bool write_force, bool from_step, bool drift,
                          int par, hipStream_t st);

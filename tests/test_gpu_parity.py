@@ -257,6 +257,51 @@ def test_matrix_screen_edges_match_oracle(k, waves, side, orc):
     _assert_rows(counts, idx, counts_o, idx_o)
 
 
+def _lattice_in(box, n):
+    """n atoms on a simple cubic lattice that fills the box."""
+    m = int(np.ceil(n ** (1 / 3) - 1e-9))
+    g = np.stack(np.meshgrid(*(np.arange(m),) * 3, indexing="ij"), -1).reshape(-1, 3)[:n]
+    pos4 = np.zeros((n, 4), np.float32)
+    pos4[:, :3] = (g + 0.5) * (box / m)
+    return pos4
+
+
+@pytest.mark.parametrize("nc,n,clump", [(3, 40, 0), (4, 300, 0), (5, 1500, 700), (17, 9000, 0), (32, 20000, 300),
+                                        (33, 20000, 300)])
+def test_load_of_shuffled_atoms_builds_exact_cells(nc, n, clump):
+    """A load in random order against a counting sort: grids of one part block
+    of 16 cells, of whole and partly filled blocks, with more atoms in one cell
+    than its bucket holds (clump), and on both sides of the largest grid whose
+    blocks are counted from the cells' counts (32^3 cells). Atoms stay clear of
+    the cell faces, so the cells are exact. Loaded twice, and once more after
+    steps that end on either counter parity."""
+    side = 2.6
+    rng = np.random.default_rng(nc)
+    cell = rng.integers(0, nc, (n, 3))
+    cell[:clump] = nc // 2
+    pos4 = np.zeros((n, 4), np.float32)
+    pos4[:, :3] = (cell + rng.uniform(0.05, 0.95, (n, 3))) * side
+    perm = rng.permutation(n)
+    pos4, cell = pos4[perm], cell[perm]
+    c = cell[:, 0] + nc * (cell[:, 1] + nc * cell[:, 2])
+    want_start = np.concatenate([[0], np.cumsum(np.bincount(c, minlength=nc**3))])
+    want_order = np.lexsort((np.arange(n), c))
+    _say(f"load nc={nc} n={n} clump={clump}")
+    s = _system(n, nc * side, cell_min=0.999 * side, dt=1e-9)
+    assert s.cells_per_dim == nc
+    x = _dev(pos4)
+    for steps in (0, 1, 2, 0):
+        s.load(x, forces=False)
+        start, order = s.cell_lists()
+        assert np.array_equal(start.cpu().numpy(), want_start), steps
+        assert np.array_equal(order.cpu().numpy(), want_order), steps
+        assert s.check() == 0
+        if steps:
+            s.load(_dev(_lattice_in(nc * side, n)))
+            s.step(steps)
+            s.check()
+
+
 @pytest.mark.parametrize("case", ["lj4k_jitter_shuffled", "lj32k_jitter", "fcc_rho1.2_jitter", "dense_clump",
                                   "cells_of_5", "cells_of_18", "cells_of_22"])
 def test_neighbor_sets_pair_lists(case, orc):
