@@ -723,7 +723,10 @@ __device__ __forceinline__ float from_lane(float v, int src) { return __int_as_f
 // N = 2,048,000 (15 atoms a cell) 324 -> 292 us, N = 256,000 53.5 -> 49.9 us (per
 // wavefront 504 matrix cycles for 804, waiting 1,270 cycles for 1,840),
 // N = 4,000 16.1 -> 14.2 us, a gas of 14 a cell 44.0 -> 42.0 us (N = 256,000),
-// 16 a cell and more (VALU before) 32.2 -> 30.1 us (N = 108,000). Up to ten atoms
+// 16 a cell and more (VALU before) 32.2 -> 30.1 us (N = 108,000). Both column
+// groups of 17..32 atoms then in one pass over the candidates, each read and
+// rounded once: whole runs another 3 to 5% (N = 4,000, 32,000 and 108,000, the
+// gas), 3% at N = 256,000, whose cells hold 14.6 +- 2. Up to ten atoms
 // keep six or more slices, whose candidates a product of sixteen columns would
 // serve less than two thirds full: the VALU screen stays there.
 typedef float mfma_f4 __attribute__((ext_vector_type(4)));
@@ -757,16 +760,15 @@ __device__ __forceinline__ HomeOps home_ops(float vx, float vy, float vz, bool o
     return h;
 }
 
-// Screen nblk <= 32 blocks of four candidates per row group: word w, bit
-// 31 - k holds the verdict on the row group's candidate 32 w + k. base: this
-// lane's candidate of the first four blocks; four blocks on, it lies 16 NS
-// entries further (NS: slices).
-template <int NS>
-__device__ __forceinline__ void screen_mfma(const float4* base, int nblk, float inv_s, const HomeOps& h,
-                                            uint32_t (&wd)[kWords]) {
-    const mfma_f4 c = {h.c, h.c, h.c, h.c};
+// Screen nblk <= 32 blocks of four candidates per row group against GROUPS
+// groups of columns: word w, bit 31 - k holds the verdict on the row group's
+// candidate 32 w + k. base: this lane's candidate of the first four blocks; four
+// blocks on, it lies 16 NS entries further (NS: slices).
+template <int NS, int GROUPS>
+__device__ __forceinline__ void screen_mfma(const float4* base, int nblk, float inv_s, const HomeOps (&h)[GROUPS],
+                                            uint32_t (&wd)[GROUPS][kWords]) {
     const float inv_s2 = inv_s * inv_s;
-    auto four = [&](int g, uint32_t& bits) {
+    auto four = [&](int g, uint32_t (&bits)[GROUPS]) {
         const float4 x = base[g * 16 * NS];
         // scaled and rounded, two values per register (in one block, with the
         // two wait states that a product needs after its operands' writes)
@@ -781,21 +783,30 @@ __device__ __forceinline__ void screen_mfma(const float4* base, int nblk, float 
         const half4 a = as_half4(lo, hi);
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const mfma_f4 d = __builtin_amdgcn_mfma_f32_16x16x16f16(a, h.b[u], c, 0, 0, 0);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) bits = __builtin_amdgcn_alignbit(bits, __float_as_uint(d[q]), 31);
+            for (int e = 0; e < GROUPS; ++e) {
+                const mfma_f4 c = {h[e].c, h[e].c, h[e].c, h[e].c};
+                const mfma_f4 d = __builtin_amdgcn_mfma_f32_16x16x16f16(a, h[e].b[u], c, 0, 0, 0);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) bits[e] = __builtin_amdgcn_alignbit(bits[e], __float_as_uint(d[q]), 31);
+            }
         }
     };
     // straight-line code per word: all LDS offsets are immediates
 #pragma unroll
     for (int w = 0; w < kWords; ++w) {
-        uint32_t bits = 0;
+        uint32_t bits[GROUPS] = {};
         if (nblk > 8 * w) {  // uniform
             four(2 * w, bits);
-            if (nblk > 8 * w + 4) four(2 * w + 1, bits);  // may run past nblk: padding
-            else bits <<= 16;
+            if (nblk > 8 * w + 4) {  // may run past nblk: padding
+                four(2 * w + 1, bits);
+            } else {
+#pragma unroll
+                for (int e = 0; e < GROUPS; ++e) bits[e] <<= 16;
+            }
         }
-        wd[w] = bits;
+#pragma unroll
+        for (int e = 0; e < GROUPS; ++e) wd[e][w] = bits[e];
     }
 }
 
@@ -811,30 +822,33 @@ __device__ __forceinline__ void screen_home(const SimArgs& a, const float4* tile
     const int gq = g0 + 4 * (lane >> 4) + q;      // ... of the block of its lane group
     const float vx = x * a.inv_s, vy = y * a.inv_s, vz = z * a.inv_s;
     if (hl.ns == 4) {
-        screen_mfma<4>(tile + 4 * gq + r, nblk, a.inv_s, home_ops(vx, vy, vz, hl.act, bound16), wd);
+        const HomeOps ops[1] = {home_ops(vx, vy, vz, hl.act, bound16)};
+        uint32_t v[1][kWords];
+        screen_mfma<4, 1>(tile + 4 * gq + r, nblk, a.inv_s, ops, v);
+#pragma unroll
+        for (int w = 0; w < kWords; ++w) wd[w] = v[0][w];
         return;
     }
     const int part = hl.ns == 2 ? r >> 1 : 0, slice = hl.ns == 2 ? r & 1 : r;
     const float4* base = tile + hl.ns * (gq + 4 * nblk * part) + slice;
     // atom h's words lie in lane h % 16 + 16 (row group of its slice and half)
     const int src = (hl.h & 15) + 16 * (hl.act ? hl.s : 0);
+    const int e = lane & 15;  // lane e of the chunk holds atom e (slice 0)
+    const HomeOps ops[2] = {home_ops(from_lane(vx, e), from_lane(vy, e), from_lane(vz, e), true, bound16),
+                            home_ops(from_lane(vx, e + 16), from_lane(vy, e + 16), from_lane(vz, e + 16), e + 16 < nh,
+                                     bound16)};
+    uint32_t v[2][kWords];
+    if (hl.ns == 3) screen_mfma<3, 2>(base, nblk, a.inv_s, ops, v);
+    else screen_mfma<2, 2>(base, nblk, a.inv_s, ops, v);
+    const bool second = hl.h >= 16;
 #pragma unroll
-    for (int w = 0; w < kWords; ++w) wd[w] = wd2[w] = 0;
-    for (int e0 = 0; e0 < nh; e0 += 16) {  // two groups of columns
-        const int e = e0 + (lane & 15);  // lane e holds atom e (slice 0)
-        const HomeOps ops = home_ops(from_lane(vx, e), from_lane(vy, e), from_lane(vz, e), e < nh, bound16);
-        uint32_t v[kWords];
-        if (hl.ns == 3) screen_mfma<3>(base, nblk, a.inv_s, ops, v);
-        else screen_mfma<2>(base, nblk, a.inv_s, ops, v);
-        const bool mine = hl.act && (hl.h & ~15) == e0;
-#pragma unroll
-        for (int w = 0; w < kWords; ++w) {
-            const uint32_t lo = from_lane(v[w], src);
-            wd[w] = mine ? lo : wd[w];
-            if (hl.ns == 2) {
-                const uint32_t hi = from_lane(v[w], src + 32);
-                wd2[w] = mine ? hi : wd2[w];
-            }
+    for (int w = 0; w < kWords; ++w) {
+        const uint32_t lo = from_lane(v[0][w], src), hi = from_lane(v[1][w], src);
+        wd[w] = hl.act ? (second ? hi : lo) : 0;
+        wd2[w] = 0;
+        if (hl.ns == 2) {
+            const uint32_t lo2 = from_lane(v[0][w], src + 32), hi2 = from_lane(v[1][w], src + 32);
+            wd2[w] = hl.act ? (second ? hi2 : lo2) : 0;
         }
     }
 }
