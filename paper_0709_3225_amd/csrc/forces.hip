@@ -463,8 +463,8 @@ __global__ void __launch_bounds__(kWave) k_forces_record(SimArgs a) {
 // s taking entry groups s, s + kListLanes, ...: partner j at x_j + s L (s
 // from the entry's image code), the truncated, shifted force of section 2
 // for r < r_c; the lanes' partials are added in a fixed order, then the
-// first lane of each atom applies the kick and the next half kick and drift
-// as the cell passes do (BIN: wrap and bin for the next rebuild; else
+// first wavefront applies the kick and the next half kick and drift as the
+// cell passes do (BIN: wrap and bin for the next rebuild; else
 // unwrapped into pos2/vel2 with the displacement check against the
 // positions the lists were written at). The displacement is formed as
 // (x_i - max(sL, 0)) - (x_j + min(sL, 0)): an image shift is taken off the
@@ -558,13 +558,24 @@ __global__ void __launch_bounds__(kListBlock) k_nlist_forces(SimArgs a) {
         fy += __shfl_xor(fy, off);
         fz += __shfl_xor(fz, off);
     }
-    // the epilogue on one lane per atom: atom lane l of the wave's 16 from lane
-    // kListLanes * l, so that consecutive atoms sit in consecutive lanes (the
-    // binning's runs)
-    const int src = (lane * kListLanes) & (kWave - 1);
-    const float gx = __shfl(fx, src), gy = __shfl(fy, src), gz = __shfl(fz, src);
-    const int ia = (i - static_cast<int>(threadIdx.x % kWave) / kListLanes) + lane;  // the wave's first atom + lane
-    const bool own = lane < kWave / kListLanes && ia < a.n;
+    // the epilogue on one lane per atom, all of them in the first wavefront: its
+    // 64 consecutive atoms are the binning's runs, and their loads and stores
+    // whole lines. With 16 atoms in each wavefront (four times the atomics and
+    // their round trips) the pass took, at N = 256,000, 23.2 us with binning for
+    // 14.8 and 12.4 without for 11.5 (14 entries an atom), 42.1 for 36.8 and 35.9
+    // for 35.0 (88 entries, bound by the gathers' address units).
+    __shared__ float fsum[3][kListAtoms];
+    if (sl == 0) {
+        const int l = static_cast<int>(threadIdx.x) / kListLanes;
+        fsum[0][l] = fx;
+        fsum[1][l] = fy;
+        fsum[2][l] = fz;
+    }
+    __syncthreads();
+    if (threadIdx.x >= kWave) return;
+    const float gx = fsum[0][lane], gy = fsum[1][lane], gz = fsum[2][lane];
+    const int ia = xcd_block_order(blockIdx.x, gridDim.x) * kListAtoms + lane;
+    const bool own = ia < a.n;
     bool bad = false;
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f), p_next = v;
     if (own) {

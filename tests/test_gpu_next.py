@@ -342,6 +342,26 @@ def test_step_nlist_tracks_oracle_and_step_every(orc, cell_min, every):
     assert rel_l2(fn[:, :3].astype(np.float64), fo) <= FORCE_TOL
 
 
+@pytest.mark.parametrize("n", [3968, 3969, 3999])
+def test_step_nlist_on_ragged_sizes(n, orc):
+    """Atom counts that are and are not whole workgroups of 64 atoms (62 of
+    them, and 1 and 31 atoms more): 7 steps with rebuilds every 3, so that
+    list steps end in both epilogues, against md_step_every within the bound
+    of the longer runs (1e-4), and the final forces against the oracle."""
+    w = ljsynth.WORKLOADS["lj4k"]
+    pos4, vel4, box = ljsynth.make_state(w, jitter_amp=0.05)
+    _say(f"md_step_nlist ragged n={n}")
+    out = _run_modes(pos4[:n], vel4[:n], box, n, 2.9, 7, 3, ("every", "nlist"))
+    pe = out["every"][1]
+    _, pn, _, fn, flags = out["nlist"]
+    assert flags == 0
+    d = pn[:, :3] - pe[:, :3]
+    d -= box * np.round(d / box)
+    assert np.abs(d).max() < 1e-4
+    fo, _, _ = orc.forces(orc.params(box), pn)
+    assert rel_l2(fn[:, :3].astype(np.float64), fo) <= FORCE_TOL
+
+
 def test_step_nlist_full_size():
     """N = 256,000 on the 24^3 grid (0.30 sigma margin; the jittered start
     moves some atoms by more than half the default grid's 0.084 sigma within
