@@ -192,9 +192,9 @@ __global__ void __launch_bounds__(MW * kWave)
             __syncthreads();
             const int self_t = home_pos + h0 + h - t0;
             const uint32_t pad = lds_address(tile + tn);
-            for_each_words<false>(a, tile, tn, hl, nh, xi, yi, zi, a.screen2, a.screen16, self_t, wv, nw,
-                           [](uint32_t (&)[kWords], int) { return false; },
-                           [&](uint32_t (&wd)[kWords], int first, int, bool) {
+            for_each_words<false, kLongWords>(a, tile, tn, hl, nh, xi, yi, zi, a.screen2, a.screen16, self_t, wv, nw,
+                           [](auto&, int) { return false; },
+                           [&](auto& wd, int first, int, bool) {
                 if constexpr (ADJ) {
                     AdjOp op{kc, lds_address(wtile) - lds_address(tile), xi, yi, zi, wi.x, wi.y, wi.z};
                     op.jx = v0; op.jy = v1; op.jz = v2; op.fx = v3; op.fy = v4; op.fz = v5; op.sg = v6;

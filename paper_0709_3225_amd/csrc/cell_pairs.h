@@ -605,6 +605,13 @@ __device__ __forceinline__ void stage_codes(const SimArgs& a, const Neighbourhoo
 // timing.
 constexpr int kWords = 4;              // accept words per lane per span
 constexpr int kGroups = 32 * kWords;   // candidates per lane of one walk
+// Words of a walk of three slices (17..21 atoms a cell), where the words are not
+// kept: four, 128 candidates a slice, leave a second walk of a few candidates to
+// neighbourhoods of 27 x 15 atoms and more; five reach 27 x 17.7. Measured with
+// four, five and six (one more select per candidate each): N = 4,000 838, 825 and
+// 816 us for 50 steps, N = 108,000 (rho 1.0) 616, 586 and 593 for 20, N = 256,000
+// 1042, 1027 and 1035 for 20.
+constexpr int kLongWords = 5;
 constexpr int kMaxSlices = 16;
 constexpr int kScreenUnroll = 4;
 constexpr int kTilePad = kMaxSlices * (kScreenUnroll + 1);  // far-away entries after the staged atoms
@@ -760,13 +767,13 @@ __device__ __forceinline__ HomeOps home_ops(float vx, float vy, float vz, bool o
     return h;
 }
 
-// Screen nblk <= 32 blocks of four candidates per row group against GROUPS
+// Screen nblk <= 8 WORDS blocks of four candidates per row group against GROUPS
 // groups of columns: word w, bit 31 - k holds the verdict on the row group's
 // candidate 32 w + k. base: this lane's candidate of the first four blocks; four
 // blocks on, it lies 16 NS entries further (NS: slices).
-template <int NS, int GROUPS>
+template <int NS, int GROUPS, int WORDS>
 __device__ __forceinline__ void screen_mfma(const float4* base, int nblk, float inv_s, const HomeOps (&h)[GROUPS],
-                                            uint32_t (&wd)[GROUPS][kWords]) {
+                                            uint32_t (&wd)[GROUPS][WORDS]) {
     const float inv_s2 = inv_s * inv_s;
     auto four = [&](int g, uint32_t (&bits)[GROUPS]) {
         const float4 x = base[g * 16 * NS];
@@ -794,7 +801,7 @@ __device__ __forceinline__ void screen_mfma(const float4* base, int nblk, float 
     };
     // straight-line code per word: all LDS offsets are immediates
 #pragma unroll
-    for (int w = 0; w < kWords; ++w) {
+    for (int w = 0; w < WORDS; ++w) {
         uint32_t bits[GROUPS] = {};
         if (nblk > 8 * w) {  // uniform
             four(2 * w, bits);
@@ -810,45 +817,44 @@ __device__ __forceinline__ void screen_mfma(const float4* base, int nblk, float 
     }
 }
 
-// Accept words of one span of a chunk of 11..32 home atoms, in the walk's
-// layout. x, y, z: this lane's home atom (frame); g0: the span's first
-// candidate of each slice, nblk: its blocks (per half with two slices). wd2:
-// the words of the second half (two slices).
+// Accept words of one span of a chunk of 11..16 (NS = 4), 17..21 (3) or 22..32 (2)
+// home atoms, in the walk's layout. x, y, z: this lane's home atom (frame); g0:
+// the span's first candidate of each slice, nblk: its blocks (per half with two
+// slices). wd2: the words of the second half (two slices).
+template <int NS, int WORDS>
 __device__ __forceinline__ void screen_home(const SimArgs& a, const float4* tile, const HomeLanes& hl, int nh, int g0,
                                             int nblk, float x, float y, float z, float bound16,
-                                            uint32_t (&wd)[kWords], uint32_t (&wd2)[kWords]) {
+                                            uint32_t (&wd)[WORDS], uint32_t (&wd2)[WORDS]) {
     const int lane = lane_here();
     const int q = lane & 3, r = (lane >> 2) & 3;  // this lane's row of A: candidate q of row group r
     const int gq = g0 + 4 * (lane >> 4) + q;      // ... of the block of its lane group
     const float vx = x * a.inv_s, vy = y * a.inv_s, vz = z * a.inv_s;
-    if (hl.ns == 4) {
+    if constexpr (NS == 4) {
         const HomeOps ops[1] = {home_ops(vx, vy, vz, hl.act, bound16)};
-        uint32_t v[1][kWords];
-        screen_mfma<4, 1>(tile + 4 * gq + r, nblk, a.inv_s, ops, v);
+        uint32_t v[1][WORDS];
+        screen_mfma<4>(tile + 4 * gq + r, nblk, a.inv_s, ops, v);
 #pragma unroll
-        for (int w = 0; w < kWords; ++w) wd[w] = v[0][w];
-        return;
-    }
-    const int part = hl.ns == 2 ? r >> 1 : 0, slice = hl.ns == 2 ? r & 1 : r;
-    const float4* base = tile + hl.ns * (gq + 4 * nblk * part) + slice;
-    // atom h's words lie in lane h % 16 + 16 (row group of its slice and half)
-    const int src = (hl.h & 15) + 16 * (hl.act ? hl.s : 0);
-    const int e = lane & 15;  // lane e of the chunk holds atom e (slice 0)
-    const HomeOps ops[2] = {home_ops(from_lane(vx, e), from_lane(vy, e), from_lane(vz, e), true, bound16),
-                            home_ops(from_lane(vx, e + 16), from_lane(vy, e + 16), from_lane(vz, e + 16), e + 16 < nh,
-                                     bound16)};
-    uint32_t v[2][kWords];
-    if (hl.ns == 3) screen_mfma<3, 2>(base, nblk, a.inv_s, ops, v);
-    else screen_mfma<2, 2>(base, nblk, a.inv_s, ops, v);
-    const bool second = hl.h >= 16;
+        for (int w = 0; w < WORDS; ++w) wd[w] = v[0][w];
+    } else {
+        const int part = NS == 2 ? r >> 1 : 0, slice = NS == 2 ? r & 1 : r;
+        const float4* base = tile + NS * (gq + 4 * nblk * part) + slice;
+        // atom h's words lie in lane h % 16 + 16 (row group of its slice and half)
+        const int src = (hl.h & 15) + 16 * (hl.act ? hl.s : 0);
+        const int e = lane & 15;  // lane e of the chunk holds atom e (slice 0)
+        const HomeOps ops[2] = {home_ops(from_lane(vx, e), from_lane(vy, e), from_lane(vz, e), true, bound16),
+                                home_ops(from_lane(vx, e + 16), from_lane(vy, e + 16), from_lane(vz, e + 16),
+                                         e + 16 < nh, bound16)};
+        uint32_t v[2][WORDS];
+        screen_mfma<NS>(base, nblk, a.inv_s, ops, v);
+        const bool second = hl.h >= 16;
 #pragma unroll
-    for (int w = 0; w < kWords; ++w) {
-        const uint32_t lo = from_lane(v[0][w], src), hi = from_lane(v[1][w], src);
-        wd[w] = hl.act ? (second ? hi : lo) : 0;
-        wd2[w] = 0;
-        if (hl.ns == 2) {
-            const uint32_t lo2 = from_lane(v[0][w], src + 32), hi2 = from_lane(v[1][w], src + 32);
-            wd2[w] = hl.act ? (second ? hi2 : lo2) : 0;
+        for (int w = 0; w < WORDS; ++w) {
+            const uint32_t lo = from_lane(v[0][w], src), hi = from_lane(v[1][w], src);
+            wd[w] = hl.act ? (second ? hi : lo) : 0;
+            if (NS == 2) {
+                const uint32_t lo2 = from_lane(v[0][w], src + 32), hi2 = from_lane(v[1][w], src + 32);
+                wd2[w] = hl.act ? (second ? hi2 : lo2) : 0;
+            }
         }
     }
 }
@@ -889,9 +895,10 @@ __device__ __forceinline__ void screen_home32(const float4* tile, const HomeLane
 }
 
 // Drop the verdicts past the first n candidates (uniform) of a lane's words.
-__device__ __forceinline__ void keep_first(int n, uint32_t (&wd)[kWords]) {
+template <int WORDS>
+__device__ __forceinline__ void keep_first(int n, uint32_t (&wd)[WORDS]) {
 #pragma unroll
-    for (int w = 0; w < kWords; ++w) {
+    for (int w = 0; w < WORDS; ++w) {
         const int valid = n - 32 * w;
         wd[w] &= valid >= 32 ? ~0u : (valid <= 0 ? 0u : ~0u << (32 - valid));
     }
@@ -929,17 +936,18 @@ __device__ __forceinline__ int wave_max(int v) {
 // The accepted candidates of one set of words in order, as LDS byte addresses:
 // the word's candidate 0 lies at wb, candidates cstep bytes apart. A lane that
 // has spent its bits gets pad, the address of the padding entry past every
-// staged atom. The words rotate through four registers (never indexed, which
+// staged atom. The words rotate through registers (never indexed, which
 // would put them in scratch memory); an exhausted word is replaced by the next
 // one without a branch.
+template <int WORDS>
 struct BitWalk {
-    uint32_t wb, wstep, cstep, pad, m, n1, n2, n3;
+    uint32_t wb, wstep, cstep, pad, m, more[WORDS - 1];
     __device__ __forceinline__ uint32_t next() {
         const bool turn = (m == 0u);
-        m = turn ? n1 : m;
-        n1 = turn ? n2 : n1;
-        n2 = turn ? n3 : n2;
-        n3 = turn ? 0u : n3;
+        m = turn ? more[0] : m;
+#pragma unroll
+        for (int w = 0; w < WORDS - 2; ++w) more[w] = turn ? more[w + 1] : more[w];
+        more[WORDS - 2] = turn ? 0u : more[WORDS - 2];
         wb += turn ? wstep : 0u;
         // all ones for a spent lane (m = 0): its shift clears no bit of m, and
         // its address (16 bits of ones times 16 to 256 bytes, which cannot
@@ -958,16 +966,18 @@ struct BitWalk {
 // step's arithmetic, so their latency is covered (two register sets take
 // turns, which saves copying them). The trip count is the busiest lane's,
 // reduced once, so the loop needs no test on the lanes.
-template <class Op>
-__device__ __forceinline__ void walk_bits(int ns, uint32_t wb0, uint32_t pad, const uint32_t (&wd)[kWords], Op& op) {
+template <int WORDS, class Op>
+__device__ __forceinline__ void walk_bits(int ns, uint32_t wb0, uint32_t pad, const uint32_t (&wd)[WORDS], Op& op) {
     const uint32_t cstep = static_cast<uint32_t>(ns) * sizeof(float4);
     // a lane's steps: its bits, and one for each empty word before its last bit
-    int steps = __builtin_popcount(wd[3]);
+    int steps = __builtin_popcount(wd[WORDS - 1]);
 #pragma unroll
-    for (int w = kWords - 2; w >= 0; --w) steps += max(__builtin_popcount(wd[w]), min(steps, 1));
+    for (int w = WORDS - 2; w >= 0; --w) steps += max(__builtin_popcount(wd[w]), min(steps, 1));
     const int trips = wave_max(steps);
     if (trips == 0) return;
-    BitWalk b{wb0, 32u * cstep, cstep, pad, wd[0], wd[1], wd[2], wd[3]};
+    BitWalk<WORDS> b{wb0, 32u * cstep, cstep, pad, wd[0], {}};
+#pragma unroll
+    for (int w = 1; w < WORDS; ++w) b.more[w - 1] = wd[w];
     auto load = [&](typename Op::Entry (&q)[2]) {
         const uint32_t a0 = b.next(), a1 = b.next();
         q[0] = op.load(a0);
@@ -997,11 +1007,12 @@ __device__ __forceinline__ void walk_bits(int ns, uint32_t wb0, uint32_t pad, co
 // words' candidates, if it lies in this lane's slice (own). The atoms of a cell
 // are neighbours in the tile, so one or two words are touched: each is skipped
 // unless some lane's bit lies in it.
-__device__ __forceinline__ void clear_self(int g, bool own, uint32_t (&wd)[kWords]) {
+template <int WORDS>
+__device__ __forceinline__ void clear_self(int g, bool own, uint32_t (&wd)[WORDS]) {
     const uint32_t bit = 0x80000000u >> (g & 31);
     const int w = own ? g >> 5 : -1;
 #pragma unroll
-    for (int i = 0; i < kWords; ++i)
+    for (int i = 0; i < WORDS; ++i)
         if (__any(w == i)) wd[i] &= w == i ? ~bit : ~0u;
 }
 
@@ -1012,8 +1023,8 @@ __device__ __forceinline__ void clear_self(int g, bool own, uint32_t (&wd)[kWord
 // bound, bound16: the screens' bounds (EXACT: only the first is used);
 // self_t: its tile index (may be outside); wv, nw: this wavefront takes the
 // wv-th of nw contiguous ranges of the candidates. kept(wd, n): true if it
-// supplied the words itself.
-template <bool EXACT, class Kept, class Fn>
+// supplied the words itself. LONG: the words of a walk with three slices.
+template <bool EXACT, int LONG, class Kept, class Fn>
 __device__ __forceinline__ void for_each_words(const SimArgs& a, const float4* tile, int tn, const HomeLanes& hl,
                                                int nh, float x, float y, float z, float bound, float bound16,
                                                int self_t, int wv, int nw, Kept kept, Fn fn) {
@@ -1041,39 +1052,47 @@ __device__ __forceinline__ void for_each_words(const SimArgs& a, const float4* t
         }
     }
     if (mat) {
-        const int span = ns == 2 ? 2 * kGroups : kGroups;
-        for (int g0 = g_lo; g0 < g_hi; g0 += span) {
-            const int groups = min(span, g_hi - g0);
-            const int blocks = (groups + 3) >> 2;
-            // per half: whole steps of the screen (four blocks), so the first
-            // half does not run into the second
-            const int nblk = ns == 2 ? ((blocks + 7) >> 3) << 2 : blocks;
-            uint32_t wd[kWords], wd2[kWords];
-            const int n1 = min(groups, 4 * nblk);
-            const bool had = kept(wd, n1);
-            if (!had) {
-                if (EXACT) screen_home32(tile, hl, g0, nblk, x, y, z, bound, wd);
-                else screen_home(a, tile, hl, nh, g0, nblk, x, y, z, bound16, wd, wd2);
-                if (nw > 1 && !four) keep_first(n1, wd);  // the screen's last step may be the next range's
-                // the home atom's own slice and number, from its tile index
-                const int c = self_t - g0 * ns;
-                if (EXACT || four) {
-                    clear_self(c >> 2, (c & 3) == hl.s, wd);
-                } else if (c >= 0) {
-                    const int g = ns == 3 ? static_cast<int>((static_cast<uint32_t>(c) * 43691u) >> 17) : c >> 1;
-                    const bool own = hl.act && c - g * ns == hl.s;
-                    clear_self(g < 4 * nblk ? g : -1, own, wd);
-                    if (ns == 2) clear_self(g - 4 * nblk, own, wd2);
+        // spans of W words (a half of the span each with two slices)
+        auto spans = [&](auto slices, auto words) {
+            constexpr int NS = decltype(slices)::value, W = decltype(words)::value;
+            constexpr int span = (NS == 2 ? 2 : 1) * 32 * W;
+            for (int g0 = g_lo; g0 < g_hi; g0 += span) {
+                const int groups = min(span, g_hi - g0);
+                const int blocks = (groups + 3) >> 2;
+                // per half: whole steps of the screen (four blocks), so the first
+                // half does not run into the second
+                const int nblk = NS == 2 ? ((blocks + 7) >> 3) << 2 : blocks;
+                uint32_t wd[W], wd2[W];
+                const int n1 = min(groups, 4 * nblk);
+                const bool had = kept(wd, n1);
+                if (!had) {
+                    if constexpr (EXACT) screen_home32(tile, hl, g0, nblk, x, y, z, bound, wd);
+                    else screen_home<NS>(a, tile, hl, nh, g0, nblk, x, y, z, bound16, wd, wd2);
+                    if (nw > 1 && NS != 4) keep_first(n1, wd);  // the screen's last step may be the next range's
+                    // the home atom's own slice and number, from its tile index
+                    const int c = self_t - g0 * NS;
+                    if (NS == 4) {
+                        clear_self(c >> 2, (c & 3) == hl.s, wd);
+                    } else if (c >= 0) {
+                        const int g = c / NS;
+                        const bool own = hl.act && c - g * NS == hl.s;
+                        clear_self(g < 4 * nblk ? g : -1, own, wd);
+                        if (NS == 2) clear_self(g - 4 * nblk, own, wd2);
+                    }
+                }
+                const int first = g0 * NS + (hl.act ? hl.s : 0);
+                fn(wd, first, n1, had);
+                if (NS == 2 && groups > n1) {
+                    if (!had) keep_first(groups - n1, wd2);  // likewise
+                    const bool had2 = kept(wd2, groups - n1);
+                    fn(wd2, first + 4 * nblk * NS, groups - n1, had2);
                 }
             }
-            const int first = g0 * ns + (hl.act ? hl.s : 0);
-            fn(wd, first, n1, had);
-            if (!EXACT && ns == 2 && groups > n1) {
-                if (!had) keep_first(groups - n1, wd2);  // likewise
-                const bool had2 = kept(wd2, groups - n1);
-                fn(wd2, first + 4 * nblk * ns, groups - n1, had2);
-            }
-        }
+        };
+        using std::integral_constant;
+        if (EXACT || ns == 4) spans(integral_constant<int, 4>{}, integral_constant<int, kWords>{});
+        else if (ns == 3) spans(integral_constant<int, 3>{}, integral_constant<int, LONG>{});
+        else spans(integral_constant<int, 2>{}, integral_constant<int, kWords>{});
         return;
     }
     const float ai = fmaf(z, z, fmaf(y, y, x * x));

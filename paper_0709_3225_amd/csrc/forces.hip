@@ -259,16 +259,22 @@ __device__ __forceinline__ void force_cell(const SimArgs& a, int c, float4* tile
             const int self_t = home_pos + h0 + h - t0;  // the home atom's own tile index (may be outside)
             const uint32_t tile0 = lds_address(tile);
             const uint32_t pad = tile0 + static_cast<uint32_t>(tn) * sizeof(float4);
-            auto kept = [&](uint32_t (&wd)[kWords], int groups) {
-                if (!(LIST == 2 && use_list)) return false;
-                kept_words(lwords, lw0, n_rec++, groups, wd);
-                return true;
+            auto kept = [&](auto& wd, int groups) {
+                if constexpr (LIST == 2) {
+                    if (use_list) kept_words(lwords, lw0, n_rec++, groups, wd);
+                    return use_list;
+                }
+                return false;
             };
-            for_each_words<LIST == 3>(a, tile, tn, hl, nh, xi, yi, zi, bound, bound16, self_t, wv, nw, kept,
-                           [&](uint32_t (&wd)[kWords], int first, int, bool) {
-                if (LIST == 1 && list_fits) keep_words(lwords, n_rec, wd);
+            // the words of a walk are kept as they are: spans of kWords
+            constexpr int kLong = LIST == 0 ? kLongWords : kWords;
+            for_each_words<LIST == 3, kLong>(a, tile, tn, hl, nh, xi, yi, zi, bound, bound16, self_t, wv, nw, kept,
+                           [&](auto& wd, int first, int, bool) {
+                if constexpr (LIST == 1) {
+                    if (list_fits) keep_words(lwords, n_rec, wd);
+                }
                 const uint32_t wb0 = tile0 + static_cast<uint32_t>(first) * sizeof(float4);
-                if (LIST == 3) {
+                if constexpr (LIST == 3) {
                     // this lane's first entry for the accepted candidates
                     // (after those of the atom's lower slices)
                     const int cnt = __popc(wd[0]) + __popc(wd[1]) + __popc(wd[2]) + __popc(wd[3]);
@@ -287,7 +293,7 @@ __device__ __forceinline__ void force_cell(const SimArgs& a, int c, float4* tile
                     fz = op.fz;
                     u_loc = op.u_loc;
                     w_loc = op.w_loc;
-                } else if (EXPORT) {
+                } else if constexpr (EXPORT) {
                     ExportOp op{a, tile0, reinterpret_cast<const char*>(raw), xi, yi, zi, __float_as_int(pi.w), ex};
                     walk_bits(ns, wb0, pad, wd, op);
                     over = over || op.over;
