@@ -49,17 +49,24 @@ __device__ __forceinline__ PairConsts pair_consts(const SimArgs& a) {
 // sigma times the sigma derivative projected on w_i.
 struct AdjOp {
     const PairConsts& k;
-    uint32_t wdelta;    // LDS distance from the position tile to the adjoint-vector tile
+    // the adjoint vector of the position at LDS address p is at (3 p + wbase) / 4
+    // (entries of 12 bytes, at three quarters of the positions' offsets)
+    uint32_t wbase;
     float xi, yi, zi, wx, wy, wz;
     float jx = 0.f, jy = 0.f, jz = 0.f, fx = 0.f, fy = 0.f, fz = 0.f, sg = 0.f;
     struct Entry {
-        float4 q, w;
+        float4 q;
+        Float3 w;
     };
-    __device__ __forceinline__ Entry load(uint32_t addr) const { return Entry{lds_load(addr), lds_load(addr + wdelta)}; }
+    __device__ __forceinline__ Entry load(uint32_t addr) const {
+        const uint32_t at = (__umul24(addr, 3u) + wbase) >> 2;
+        const auto* p = (const __attribute__((address_space(3))) float*)(static_cast<uintptr_t>(at));
+        return Entry{lds_load(addr), Float3{p[0], p[1], p[2]}};
+    }
     __device__ __forceinline__ void operator()(const Entry& e) {
-        const float4 q = e.q, wj = e.w;
+        const float4 q = e.q;
+        const Float3 wj = e.w;
         keep(q.w);
-        keep(wj.w);
         const float dx = xi - q.x, dy = yi - q.y, dz = zi - q.z;
         const float r2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
         const bool ok = r2 < k.rc2;
@@ -120,6 +127,9 @@ struct VGradOp {
 // One pass over the pairs of every home cell: the Hessian-vector product
 // (ADJ) or the virial gradient (VGRAD). Staging and screen as in the force
 // kernel, with the adjoint vector (ADJ) in a second tile at the same indices.
+// LDS bounds ADJ's wavefronts per CU: vectors of 12 bytes let nine cells of the
+// liquid onto a CU where 16 bytes let eight, so that N = 32,000 (2,197 cells, 8.6
+// a CU) runs in one round: 20.1 -> 16.9 us a pass (N = 100,003: 37.4, as before).
 // The slice
 // reduction reuses the tiles. With nw = blockDim / 64 <= MW wavefronts per
 // cell, wavefront 0 stages, each screens and walks its own contiguous range
@@ -135,9 +145,9 @@ __global__ void __launch_bounds__(MW * kWave)
     }
     constexpr bool ADJ = (OP == OP_ADJ);
     constexpr int NRED = ADJ ? 7 : 5;  // partials per lane
-    extern __shared__ float4 tile[];  // positions, then (ADJ) the adjoint vector: 2 x (tile_cap + kTilePad)
+    extern __shared__ float4 tile[];  // tile_cap + kTilePad positions, then (ADJ) as many adjoint vectors of 12 bytes
     __shared__ Neighbourhood nb;
-    float4* wtile = tile + (a.tile_cap + kTilePad);
+    Float3* wtile = reinterpret_cast<Float3*>(tile + (a.tile_cap + kTilePad));
     float* red = reinterpret_cast<float*>(tile);  // NRED x 64 floats per wavefront, after the walk
     const int lane = __lane_id();
     const int wv = MW == 1 ? 0 : static_cast<int>(threadIdx.x) >> 6;  // uniform per wavefront
@@ -186,7 +196,7 @@ __global__ void __launch_bounds__(MW * kWave)
             if (wv == 0) {
                 for (int t = lane; t < kTilePad; t += kWave) {
                     tile[tn + t] = pad_entry(a);
-                    if (ADJ) wtile[tn + t] = make_float4(0.f, 0.f, 0.f, 0.f);
+                    if (ADJ) wtile[tn + t] = Float3{0.f, 0.f, 0.f};
                 }
             }
             __syncthreads();
@@ -196,7 +206,7 @@ __global__ void __launch_bounds__(MW * kWave)
                            [](auto&, int) { return false; },
                            [&](auto& wd, int first, int, bool) {
                 if constexpr (ADJ) {
-                    AdjOp op{kc, lds_address(wtile) - lds_address(tile), xi, yi, zi, wi.x, wi.y, wi.z};
+                    AdjOp op{kc, 4 * lds_address(wtile) - 3 * lds_address(tile), xi, yi, zi, wi.x, wi.y, wi.z};
                     op.jx = v0; op.jy = v1; op.jz = v2; op.fx = v3; op.fy = v4; op.fz = v5; op.sg = v6;
                     walk_bits(ns, lds_address(tile + first), pad, wd, op);
                     v0 = op.jx; v1 = op.jy; v2 = op.jz; v3 = op.fx; v4 = op.fy; v5 = op.fz; v6 = op.sg;
@@ -360,8 +370,9 @@ __global__ void __launch_bounds__(256) k_adjoint_drift(int n, float dt, const fl
 template <int OP, class... Args>
 void launch_pair(const SimArgs& a, hipStream_t st, Args... args) {
     constexpr size_t nred = OP == OP_ADJ ? 7 : 5;
-    const size_t tiles = (OP == OP_ADJ ? 2 : 1) * static_cast<size_t>(a.tile_cap + kTilePad);
-    const size_t lds = sizeof(float4) * std::max(tiles, nred * 16 * static_cast<size_t>(a.waves));
+    const size_t entry = sizeof(float4) + (OP == OP_ADJ ? sizeof(Float3) : 0);
+    const size_t lds = std::max(entry * static_cast<size_t>(a.tile_cap + kTilePad),
+                                sizeof(float) * nred * kWave * static_cast<size_t>(a.waves));
     if (a.waves == 1)
         hipLaunchKernelGGL((k_pair_pass<OP, 1>), dim3(a.ncells), dim3(kWave), lds, st, a, args...);
     else

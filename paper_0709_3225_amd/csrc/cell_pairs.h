@@ -195,6 +195,14 @@ struct StageCursor {
     int sg, g;
 };
 
+// An entry of the vector tile: all of a float4, or its first three components
+// in 12 bytes.
+struct Float3 {
+    float x, y, z;
+};
+__device__ __forceinline__ void put(float4& d, const float4& v) { d = v; }
+__device__ __forceinline__ void put(Float3& d, const float4& v) { d = Float3{v.x, v.y, v.z}; }
+
 __device__ __forceinline__ StageCursor stage_begin(const HoodSegs& h, int t0) {
     StageCursor cur{0, t0};
     const int nseg = h.nseg();
@@ -249,9 +257,9 @@ __device__ __forceinline__ void stage_issue(const SimArgs& a, const HoodSegs& h,
 }
 
 // cur: the cursor stage_issue started from; on return, past the batch.
-template <int B, bool ID_IN_W, bool WITH_VEC>
+template <int B, bool ID_IN_W, bool WITH_VEC, class VT>
 __device__ __forceinline__ void stage_commit(const HoodSegs& h, const StageBatch<B, WITH_VEC>& b, StageCursor& cur,
-                                             int t0, int t1, float4* tile, float4* vtile) {
+                                             int t0, int t1, float4* tile, VT* vtile) {
     const int lane = __lane_id();
 #pragma unroll
     for (int u = 0; u < B; ++u) {
@@ -264,7 +272,7 @@ __device__ __forceinline__ void stage_commit(const HoodSegs& h, const StageBatch
                 const float y = b.q[u].y - lane_value(h.y, seg);
                 const float z = b.q[u].z - lane_value(h.z, seg);
                 tile[dst] = make_float4(x, y, z, ID_IN_W ? b.q[u].w : x * x + y * y + z * z);
-                if (WITH_VEC) vtile[dst] = b.vq[u];
+                if (WITH_VEC) put(vtile[dst], b.vq[u]);
             }
         }
     }
@@ -476,9 +484,9 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t slot_buffer(const float4* p, i
 // afterwards. Atoms 64 and up of a longer piece follow, masked, after every
 // piece's first 64: no surplus store reaches that far. The tile needs room for
 // total + 63 entries.
-template <int SECOND>
+template <int SECOND, class VT>
 __device__ __forceinline__ void stage_nine(const SimArgs& a, const RowHood& r, const Pieces& t, float fx, float4* tile,
-                                           float4* raw, const float4* vsrc) {
+                                           VT* raw, const float4* vsrc) {
     const int lane = lane_here();
     const uint32_t lane16 = 16u * static_cast<uint32_t>(lane);
     const __amdgpu_buffer_rsrc_t pos = slot_buffer(a.pos0, a.natoms);
@@ -493,7 +501,7 @@ __device__ __forceinline__ void stage_nine(const SimArgs& a, const RowHood& r, c
         const float y = q[k].y - r.fy[k % 3];
         const float z = q[k].z - r.fz[k / 3];
         tile[t.pos[k] + lane] = make_float4(x, y, z, x * x + y * y + z * z);
-        if (SECOND == SECOND_RAW) raw[t.pos[k] + lane] = q[k];
+        if (SECOND == SECOND_RAW) put(raw[t.pos[k] + lane], q[k]);
         if (SECOND == SECOND_CODE)
             codes[t.pos[k] + lane] = list_entry(t.first[k] + lane, sx, image_shift(r.oy, r.fy[k % 3], a.box),
                                                 image_shift(r.oz, r.fz[k / 3], a.box));
@@ -504,10 +512,10 @@ __device__ __forceinline__ void stage_nine(const SimArgs& a, const RowHood& r, c
     if (SECOND == SECOND_VEC) {  // a second round (the positions' registers are free again)
         const __amdgpu_buffer_rsrc_t vec = slot_buffer(vsrc, a.natoms);
 #pragma unroll
-        for (int k = 0; k < 9; ++k) q[k] = load_slot<true>(vec, lane16 + 16u * t.first[k]);
+        for (int k = 0; k < 9; ++k) q[k] = load_slot<std::is_same_v<VT, float4>>(vec, lane16 + 16u * t.first[k]);
 #pragma unroll
         for (int k = 0; k < 9; ++k) {
-            raw[t.pos[k] + lane] = q[k];
+            put(raw[t.pos[k] + lane], q[k]);
             __builtin_amdgcn_sched_barrier(0);
         }
     }
@@ -520,8 +528,8 @@ __device__ __forceinline__ void stage_nine(const SimArgs& a, const RowHood& r, c
                     const float4 u = a.pos0[t.first[k] + off];
                     const float x = u.x - fx, y = u.y - r.fy[k % 3], z = u.z - r.fz[k / 3];
                     tile[t.pos[k] + off] = make_float4(x, y, z, x * x + y * y + z * z);
-                    if (SECOND == SECOND_RAW) raw[t.pos[k] + off] = u;
-                    if (SECOND == SECOND_VEC) raw[t.pos[k] + off] = vsrc[t.first[k] + off];
+                    if (SECOND == SECOND_RAW) put(raw[t.pos[k] + off], u);
+                    if (SECOND == SECOND_VEC) put(raw[t.pos[k] + off], vsrc[t.first[k] + off]);
                     if (SECOND == SECOND_CODE)
                         codes[t.pos[k] + off] = list_entry(t.first[k] + off, sx, image_shift(r.oy, r.fy[k % 3], a.box),
                                                            image_shift(r.oz, r.fz[k / 3], a.box));
@@ -532,8 +540,8 @@ __device__ __forceinline__ void stage_nine(const SimArgs& a, const RowHood& r, c
 }
 
 // The whole neighbourhood of r in one pass (total <= tile capacity).
-template <int SECOND = SECOND_NONE>
-__device__ __forceinline__ void stage_hood(const SimArgs& a, const RowHood& r, float4* tile, float4* raw = nullptr,
+template <int SECOND = SECOND_NONE, class VT = float4>
+__device__ __forceinline__ void stage_hood(const SimArgs& a, const RowHood& r, float4* tile, VT* raw = nullptr,
                                            const float4* vsrc = nullptr) {
     stage_nine<SECOND>(a, r, r.a, r.ox, tile, raw, vsrc);
     if (r.face) {  // the table of the B pieces is read again (two tables do not fit the scalar registers)
@@ -548,10 +556,10 @@ __device__ __forceinline__ void stage_hood(const SimArgs& a, const RowHood& r, f
 // Stage neighbourhood atoms [t0, t0 + tn) of the table in nb (an interior
 // cell's neighbourhood costs one global round trip).
 // B chunks in flight per batch (default: 9, or 3 with a vector).
-template <bool ID_IN_W, bool WITH_VEC = false, int B = (WITH_VEC ? 3 : 9)>
+template <bool ID_IN_W, bool WITH_VEC = false, class VT = float4, int B = (WITH_VEC ? 3 : 9)>
 __device__ __forceinline__ void stage_tile(const SimArgs& a, const Neighbourhood& nb, float4* tile,
                                            int t0, int tn, const float4* vec = nullptr,
-                                           float4* vtile = nullptr) {
+                                           VT* vtile = nullptr) {
     const HoodSegs h = hood_from_lds(nb);
     if (!WITH_VEC && t0 == 0 && tn == h.total()) {
         stage_whole<ID_IN_W>(a, h, tile);
@@ -563,7 +571,7 @@ __device__ __forceinline__ void stage_tile(const SimArgs& a, const Neighbourhood
         StageBatch<B, WITH_VEC> b;
         StageCursor issue = cur;
         stage_issue(a, h, issue, t1, b, vec);
-        stage_commit<B, ID_IN_W, WITH_VEC>(h, b, cur, t0, t1, tile, vtile);
+        stage_commit<B, ID_IN_W>(h, b, cur, t0, t1, tile, vtile);
     }
 }
 
