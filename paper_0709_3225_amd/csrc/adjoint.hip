@@ -202,7 +202,7 @@ __global__ void __launch_bounds__(MW * kWave)
             __syncthreads();
             const int self_t = home_pos + h0 + h - t0;
             const uint32_t pad = lds_address(tile + tn);
-            for_each_words<false, kLongWords>(a, tile, tn, hl, nh, xi, yi, zi, a.screen2, a.screen16, self_t, wv, nw,
+            for_each_words<false, kLongWords, false>(a, tile, tn, hl, nh, xi, yi, zi, a.screen2, a.screen16, self_t, wv, nw,
                            [](auto&, int) { return false; },
                            [&](auto& wd, int first, int, bool) {
                 if constexpr (ADJ) {

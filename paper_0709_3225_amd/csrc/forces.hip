@@ -127,24 +127,42 @@ struct ExportOp {
     }
 };
 
-// Kept accept words (pair lists as bitmasks): each set of a lane's words is one
-// 16-byte record; sets past kListSpans are only counted (the cell then
-// screens).
-__device__ __forceinline__ void keep_words(uint4* rows, int& n, const uint32_t (&wd)[kWords]) {
-    if (n < kListSpans) rows[n] = make_uint4(wd[0], wd[1], wd[2], wd[3]);
+// Kept accept words (pair lists as bitmasks): each four of a lane's words are one
+// 16-byte record, and record j of a cell's 64 lanes is one run of 1 KB (a lane
+// reads the records that its cell has, not the room for all); records past
+// kListSpans are only counted (the cell then screens).
+template <int WORDS>
+__device__ __forceinline__ void keep_words(uint4* rows, int& n, int groups, const uint32_t (&wd)[WORDS]) {
+    if (n < kListSpans) rows[n * kWave] = make_uint4(wd[0], wd[1], wd[2], wd[3]);
     ++n;
+    if constexpr (WORDS > kWords) {
+        static_assert(WORDS == kWords + 2, "two records");
+        if (groups > kGroups) {  // uniform
+            if (n < kListSpans) rows[n * kWave] = make_uint4(wd[4], wd[5], 0u, 0u);
+            ++n;
+        }
+    }
 }
 
-// Record j of the kept words; record 0 was requested before the staging (w0).
-// Bits past the set's groups candidates per lane are dropped, so a walk never
-// leaves the staged span, whatever the words hold.
-__device__ __forceinline__ void kept_words(const uint4* rows, const uint4& w0, int j, int groups,
-                                           uint32_t (&wd)[kWords]) {
-    const uint4 v = j == 0 ? w0 : (j < kListSpans ? rows[j] : make_uint4(0u, 0u, 0u, 0u));
+// The kept words from record j on; record 0 and the two words of record 1 that
+// a walk of six takes were requested before the staging (w0, w1). Bits past the set's groups candidates per lane are dropped,
+// so a walk never leaves the staged span, whatever the words hold.
+template <int WORDS>
+__device__ __forceinline__ void kept_words(const uint4* rows, const uint4& w0, const uint2& w1, int& j, int groups,
+                                           uint32_t (&wd)[WORDS]) {
+    uint4 v = w0;
+    if (j > 0) v = j < kListSpans ? rows[j * kWave] : make_uint4(0u, 0u, 0u, 0u);
+    ++j;
     wd[0] = v.x;
     wd[1] = v.y;
     wd[2] = v.z;
     wd[3] = v.w;
+    if constexpr (WORDS > kWords) {  // one walk takes all candidates: the records are 0 and 1
+        const bool two = groups > kGroups;
+        wd[4] = two ? w1.x : 0u;
+        wd[5] = two ? w1.y : 0u;
+        j += two ? 1 : 0;
+    }
     keep_first(groups, wd);
 }
 
@@ -162,11 +180,11 @@ __device__ __forceinline__ void kept_words(const uint4* rows, const uint4& w0, i
 // within r_c in the 27-cell neighbourhood, section 3.1) or, with pair lists,
 // has moved more than disp_half since they were recorded (section 3).
 // LIST 1: the screen takes the list radius (the cell side) as its bound and
-// each lane's accept words are kept (one 16-byte record per span), and the
+// each lane's accept words are kept (one 16-byte record per four), and the
 // home positions go to posref. LIST 2: a lane walks its kept words instead of
 // screening: the same candidates in the same order plus some beyond r_c,
 // which add exact zeros, so the sums are bitwise those of the screen. A cell
-// with more than kListSpans spans per lane, or more than one pass, screens as
+// with more than kListSpans records per lane, or more than one pass, screens as
 // usual (and with the plain bound).
 // LIST 3: the screen takes the list radius and every candidate it accepts
 // goes to the home atom's neighbour list (raw: the staged atoms' list
@@ -210,14 +228,16 @@ __device__ __forceinline__ void force_cell(const SimArgs& a, int c, float4* tile
     double u_acc = 0.0, w_acc = 0.0, k_acc = 0.0;
     bool bad = false, skin_out = false, over = false;
     const size_t lrow = (static_cast<size_t>(a.cbase + c) * kWave + lane);  // this lane's kept words
-    uint4* lwords = reinterpret_cast<uint4*>(a.plist) + lrow * kListSpans;
+    uint4* lwords = reinterpret_cast<uint4*>(a.plist) + static_cast<size_t>(a.cbase + c) * kListSpans * kWave + lane;
     const bool list_fits = total <= a.tile_cap && n_home <= kWave;          // uniform
     int n_rec = 0;  // LIST 1, 2: sets of words kept, taken
     int list_n = 0;
-    uint4 lw0 = make_uint4(0u, 0u, 0u, 0u);  // LIST 2: the first span's words, requested before staging
+    uint4 lw0 = make_uint4(0u, 0u, 0u, 0u);  // LIST 2: the first records' words, requested before staging
+    uint2 lw1 = make_uint2(0u, 0u);
     if (LIST == 2) {
         list_n = a.plist_n[lrow];
         lw0 = lwords[0];
+        lw1 = *reinterpret_cast<const uint2*>(lwords + kWave);
     }
     const bool use_list = LIST == 2 && list_fits && __all(list_n <= kListSpans);
     for (int h0 = 0; h0 < n_home; h0 += kWave) {
@@ -261,17 +281,16 @@ __device__ __forceinline__ void force_cell(const SimArgs& a, int c, float4* tile
             const uint32_t pad = tile0 + static_cast<uint32_t>(tn) * sizeof(float4);
             auto kept = [&](auto& wd, int groups) {
                 if constexpr (LIST == 2) {
-                    if (use_list) kept_words(lwords, lw0, n_rec++, groups, wd);
+                    if (use_list) kept_words(lwords, lw0, lw1, n_rec, groups, wd);
                     return use_list;
                 }
                 return false;
             };
-            // the words of a walk are kept as they are: spans of kWords
-            constexpr int kLong = LIST == 0 ? kLongWords : kWords;
-            for_each_words<LIST == 3, kLong>(a, tile, tn, hl, nh, xi, yi, zi, bound, bound16, self_t, wv, nw, kept,
-                           [&](auto& wd, int first, int, bool) {
+            constexpr bool kKept = LIST == 1 || LIST == 2;
+            for_each_words<LIST == 3, kKept ? kKeptWords : kLongWords, kKept>(a, tile, tn, hl, nh, xi, yi, zi, bound, bound16, self_t, wv, nw, kept,
+                           [&](auto& wd, int first, int groups, bool) {
                 if constexpr (LIST == 1) {
-                    if (list_fits) keep_words(lwords, n_rec, wd);
+                    if (list_fits) keep_words(lwords, n_rec, groups, wd);
                 }
                 const uint32_t wb0 = tile0 + static_cast<uint32_t>(first) * sizeof(float4);
                 if constexpr (LIST == 3) {

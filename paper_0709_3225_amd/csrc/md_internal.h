@@ -27,10 +27,10 @@ enum : int { STATE_BUILDING = 0x4D440000, STATE_CELLS = 0x4D440001, STATE_FORCES
 constexpr int kBlockShift = 4;
 constexpr int kDirectBlocks = 2048;
 constexpr int kLoadPar = 1;  // counters a load's build uses
-// Pair lists: a cell's lanes keep the accept words of its screen (one span
+// Pair lists: a cell's lanes keep the accept words of its screen (one record
 // covers 128 candidates of a lane; a liquid-density neighbourhood of about
-// 400 atoms needs one span with four slices, two with two or three).
-constexpr int kListSpans = 4;  // kept accept-word spans (16 bytes each) per lane of a cell
+// 400 atoms needs one record with four slices, two with two or three).
+constexpr int kListSpans = 4;  // kept records of accept words (16 bytes each) per lane of a cell
 constexpr int kSlotBits = 27;  // neighbour-list entry: sorted slot, then the image shift code
 constexpr uint32_t kSlotMask = (1u << kSlotBits) - 1u;
 
@@ -52,7 +52,7 @@ struct SimArgs {
     float4* vel2;
     float skin_half;  // an atom may leave its cell's box by this much before a rebuild is due
     // Pair lists (md_step_list): per cell and lane, the accept words of the
-    // screen against the list radius (the cell side), kListSpans spans of
+    // screen against the list radius (the cell side), kListSpans records of
     // four words at most (plist_n: the count; more marks a cell that screens
     // instead); posref: positions when the words were kept.
     uint32_t* plist;

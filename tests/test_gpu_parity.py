@@ -214,15 +214,16 @@ def test_every_home_layout_matches_oracle(k, waves, orc):
 
 
 def _k_per_cell_fine(k, seed, side, nc=4):
-    """k <= 64 atoms in every cell, on sites of a 4^3 sub-lattice (spacing side
-    / 4) with a jitter of +-0.03; drawn again until no pair is within 2e-5 of
-    r_c = 2.5."""
+    """k <= 64 atoms in every cell (k: a number, or several that the cells take
+    in turn), on sites of a 4^3 sub-lattice (spacing side / 4) with a jitter of
+    +-0.03; drawn again until no pair is within 2e-5 of r_c = 2.5."""
     u = (np.arange(4) + 0.5) * side / 4
     sites = np.stack(np.meshgrid(u, u, u, indexing="ij"), -1).reshape(-1, 3)
     cells = np.stack(np.meshgrid(*(np.arange(nc),) * 3, indexing="ij"), -1).reshape(-1, 3) * side
     for attempt in range(100):
         rng = np.random.default_rng(seed + 1000 * attempt)
-        pts = np.concatenate([c + sites[rng.choice(64, size=k, replace=False)] for c in cells])
+        ks = np.resize(k, len(cells))
+        pts = np.concatenate([c + sites[rng.choice(64, size=m, replace=False)] for c, m in zip(cells, ks)])
         pos4 = np.zeros((len(pts), 4), np.float32)
         pos4[:, :3] = pts + rng.uniform(-0.03, 0.03, pts.shape)
         x = pos4[:, :3].astype(np.float64)
@@ -300,6 +301,26 @@ def test_load_of_shuffled_atoms_builds_exact_cells(nc, n, clump):
             s.load(_dev(_lattice_in(nc * side, n)))
             s.step(steps)
             s.check()
+
+
+@pytest.mark.parametrize("k", [17, 21, (20, 25), (18, 15, 12)])
+def test_kept_words_of_three_slices(k, orc):
+    """The kept accept words of cells of 17 to 21 atoms: one walk of six words
+    in two records (153 and 189 candidates a slice), spans of four where the
+    neighbourhood has more than 6 x 32 a slice (20 atoms among cells of 25),
+    and cells that need one record beside cells that need two. The sets that
+    the recording pass and the walk of the records export, against the
+    oracle's."""
+    pos4, box = _k_per_cell_fine(k, 400, 2.51)
+    _say(f"kept words k={k} n={len(pos4)}")
+    counts_o, idx_o, guard = orc.neighbors(orc.params(box), pos4)
+    assert guard == 0
+    s = _system(len(pos4), box, pair_lists=True)
+    s.load(_dev(pos4), forces=False)
+    for mode in ("record", "kept"):
+        counts, idx = s.neighbors(int(counts_o.max()) + 8, lists=mode)
+        assert s.check() == 0
+        _assert_rows(counts, idx, counts_o, idx_o)
 
 
 @pytest.mark.parametrize("case", ["lj4k_jitter_shuffled", "lj32k_jitter", "fcc_rho1.2_jitter", "dense_clump",
