@@ -596,8 +596,8 @@ __device__ __forceinline__ void stage_codes(const SimArgs& a, const Neighbourhoo
 // Cell-pair kernels. One wavefront per home cell; lane = (home atom h, slice s)
 // with ns slices per atom: four for 11..16 atoms, else floor(64 / atoms) (at
 // most 16), so that a cell of 15 atoms keeps 60 lanes busy and one of 20 atoms
-// too. The staged candidates are screened in spans of up to 128 per lane (256
-// with two slices):
+// too. The staged candidates are screened in spans of up to 128 per lane (160
+// or 192 with three slices, 256 with two):
 //  screen : lane (h, s) gets the verdicts on candidates s, s + ns, s + 2 ns, ...
 //           (slices interleave, so every slice samples the whole neighbourhood
 //           and the slices of one atom find similar numbers of partners): the
