@@ -555,8 +555,12 @@ __device__ __forceinline__ void stage_hood(const SimArgs& a, const RowHood& r, f
 
 // Stage neighbourhood atoms [t0, t0 + tn) of the table in nb (an interior
 // cell's neighbourhood costs one global round trip).
-// B chunks in flight per batch (default: 9, or 3 with a vector).
-template <bool ID_IN_W, bool WITH_VEC = false, class VT = float4, int B = (WITH_VEC ? 3 : 9)>
+// B chunks in flight per batch: 9, or with a vector 5 (the neighbour export:
+// 70.4 us with three, 69.1 with five, N = 32,000 and tiles of 192 atoms) and 3
+// for one of 12 bytes (the adjoint pass, whose registers are short: a seed at N =
+// 100,003 and tiles of 192 atoms 224 us with three, 229 with five).
+template <bool ID_IN_W, bool WITH_VEC = false, class VT = float4,
+          int B = (!WITH_VEC ? 9 : std::is_same_v<VT, float4> ? 5 : 3)>
 __device__ __forceinline__ void stage_tile(const SimArgs& a, const Neighbourhood& nb, float4* tile,
                                            int t0, int tn, const float4* vec = nullptr,
                                            VT* vtile = nullptr) {
