@@ -13,6 +13,7 @@
 
 #include "md.h"
 #include "md_internal.h"
+#include "screen_bounds.h"
 
 namespace mdlj {
 namespace {
@@ -176,27 +177,6 @@ md_status check_ws(const Layout& L, const void* ws, size_t ws_bytes) {
 
 bool aligned16(const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15) == 0; }
 
-// Screen bound: frame coordinates lie within [-s, 2s) per axis, so |x|^2 <= 12 s^2;
-// the FP32 dot-product form of r^2 errs by a few ulp of that. 2^-17 * 12 s^2 leaves a
-// wide margin, so the screen never drops a pair that the exact test accepts.
-float screen_bound(double rc, double s) { return static_cast<float>(rc * rc + std::ldexp(12.0 * s * s, -17)); }
-
-// Bound of the 16-bit screen, in units of the cell side s: (r / s)^2 plus a
-// margin above what rounding to 16 bits (half a unit of 2^-10 relative) can
-// take off a pair with r_ij <= r <= s. With home coordinates in [-d, 1 + d]
-// (atoms may leave their cell by d = (s - r_c) / 2 between rebuilds), centred
-// candidate coordinates |u| <= 1.5 + 2 d and |x_j|^2 <= (sqrt(3) (1 + d) + 1)^2:
-//   sum |u| err(2 v) + sum |2 v| err(u) + err(|x_j|^2)
-//   <= 3 (1.5 + 2 d) 2^-10 + 3 (2 + 2 d) 2^-11 + 2^-9 < 0.0095 for d < 0.05,
-//   <= 3 x 2 x 2^-10 + 3 x 2.5 x 2^-11 + 2^-8       < 0.0136 for d < 0.25
-// (d is below 0.25 only while s < 2 r_c; wider cells, up to d = 0.5: |u| < 2.5
-// and |x_j|^2 < 13, below 0.0250).
-float screen16_bound(double rc, double r, double s) {
-    const double d = 0.5 * (s - rc) / s;
-    const double margin = d < 0.05 ? 0.0100 : (d < 0.25 ? 0.0145 : 0.0260);
-    return static_cast<float>(r * r / (s * s) + margin);
-}
-
 // One LDS pass of the cell-pair kernels holds the mean 27-cell neighbourhood
 // plus 10% and half a wavefront (a liquid's neighbourhood counts vary by a few
 // percent; a larger one takes a second pass). A small tile leaves room for
@@ -277,7 +257,7 @@ SimArgs make_args(const md_params* p, const Layout& L, void* ws) {
     a.fc = p->shift_mode == 0 ? static_cast<float>(flj_rc) : 0.f;
     a.uc = static_cast<float>(ulj_rc);
     a.screen2 = screen_bound(rc, L.s);
-    a.screen16 = screen16_bound(rc, rc, L.s);
+    a.screen16 = screen16_bound(rc, L.s);
     // half the margin of the cell side over r_c, less a relative 2^-20 for the
     // FP32 comparison
     a.skin_half = static_cast<float>(std::max(0.0, 0.5 * (static_cast<double>(L.s) - rc) * (1.0 - std::ldexp(1.0, -20))));
@@ -287,7 +267,7 @@ SimArgs make_args(const md_params* p, const Layout& L, void* ws) {
     // while no atom has moved by half of r_V - r_c (less a relative 2^-20)
     const double rv = p->list_radius > 0.f ? static_cast<double>(p->list_radius) : static_cast<double>(L.s);
     a.list_screen2 = screen_bound(rv, L.s);
-    a.list_screen16 = screen16_bound(rc, rv, L.s);
+    a.list_screen16 = screen16_bound(rv, L.s);
     a.disp_half = static_cast<float>(std::max(0.0, 0.5 * (rv - rc) * (1.0 - std::ldexp(1.0, -20))));
     a.tile_cap = p->tile_cap != 0 ? p->tile_cap : tile_capacity(p->n, L.ncells);
     a.waves = waves_per_cell(p);
@@ -552,7 +532,7 @@ md_status batch_plan(const md_params* p, const md_replica* reps, int32_t count, 
         r.inv_box = 1.0f / q.box;
         r.nc_magic = division_magic(Lb.nc);
         r.screen2 = screen_bound(static_cast<double>(cutoff(&q)), Lb.s);
-        r.screen16 = screen16_bound(static_cast<double>(cutoff(&q)), static_cast<double>(cutoff(&q)), Lb.s);
+        r.screen16 = screen16_bound(static_cast<double>(cutoff(&q)), Lb.s);
         B.max_mean = std::max(B.max_mean, static_cast<double>(q.n) / Lb.ncells);
         ntot += q.n;
         ctot += Lb.ncells;
