@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 import ljsynth
+from test_gpu_parity import _assert_rows
 
 pytestmark = pytest.mark.gpu
 
@@ -73,3 +74,71 @@ def test_far_candidate_leaves_other_pairs_alone(m, nc, waves, tile, orc):
     assert s.check(raise_on_error=False) == L.MD_DEV_SKIN
     _, v, _ = orc.run(orc.params(box, dt=1 / 128), pos4, vel4, 3)
     assert rel_l2(vel.cpu().numpy()[:-1, :3], v[:-1]) < 1e-5
+
+
+def _clear_of_cutoff(x, box, rc=2.5, band=1e-5):
+    d = x[:, None] - x[None]
+    d -= box * np.round(d / box)
+    return not (np.abs(np.sqrt((d * d).sum(-1)) - rc) < band).any()
+
+
+@pytest.mark.parametrize("k,waves,side", [(13, 1, 5.2), (16, 4, 6.0), (19, 1, 6.0), (21, 2, 5.2), (25, 1, 5.2),
+                                          (32, 2, 6.0), (18, 1, 40.0)])
+def test_matrix_screen_on_wide_cells(k, waves, side, orc):
+    """Cells of more than two cutoffs, as WCA and dilute gases on cells sized by
+    occupancy have, with k atoms in each: the accepted pairs are the oracle's."""
+    rng = np.random.default_rng(k)
+    cells = np.stack(np.meshgrid(*(np.arange(4),) * 3, indexing="ij"), -1).reshape(-1, 3)
+    # k of 4^3 sites a cell, 1.3 to 1.5 apart, in the corner next to eight others
+    sites = np.stack(np.meshgrid(*(np.arange(4),) * 3, indexing="ij"), -1).reshape(-1, 3) + 0.5
+    at = min(side / 4, 1.5) * sites
+    pts = []
+    for c in cells:
+        q = at[rng.choice(64, size=k, replace=False)]
+        pts.append(c * side + np.where(c % 2 == 1, q, side - q))
+    box = 4 * side
+    for _ in range(100):
+        pos4 = np.zeros((64 * k, 4), np.float32)
+        pos4[:, :3] = np.concatenate(pts) + rng.uniform(-0.2, 0.2, (64 * k, 3))
+        if _clear_of_cutoff(pos4[:, :3].astype(np.float64), box, band=2e-5):
+            break
+    _say(f"wide cells k={k} waves={waves} side={side}")
+    counts_o, idx_o, guard = orc.neighbors(orc.params(box), pos4)
+    assert guard == 0 and counts_o.mean() > 4
+    s = _system(len(pos4), box, waves_per_cell=waves, cell_min=0.999 * side)
+    assert s.cells_per_dim == 4
+    s.load(_dev(pos4))
+    counts, idx = s.neighbors(int(counts_o.max()) + 8)
+    assert s.check() == 0
+    _assert_rows(counts, idx, counts_o, idx_o)
+
+
+@pytest.mark.parametrize("sign", [1, -1])
+@pytest.mark.parametrize("nc,side,rho", [(4, 2.67, 0.8), (3, 3.2, 0.8), (3, 5.34, 0.17)])
+def test_screen_of_atoms_outside_their_cells(nc, side, rho, sign, orc):
+    """The step between rebuilds, with the whole state moving along a diagonal
+    by 0.9 of what the cells allow: atoms at the faces lie outside their cells by
+    0.52 of it on each axis. Truncated, unshifted force: a dropped pair at r_c
+    would change a velocity by dt / 2 x 0.039 = 1.5e-4; FP32 round-off of these
+    velocities and forces stays below 3e-5."""
+    box, dt = nc * side, 1 / 128
+    p = orc.params(box, dt=dt, shift_mode=1)
+    for seed in range(100):
+        rng = np.random.default_rng(seed)
+        m = int(np.ceil((rho * box ** 3) ** (1 / 3)))
+        g = np.stack(np.meshgrid(*(np.arange(m),) * 3, indexing="ij"), -1).reshape(-1, 3)
+        pos4 = np.zeros((m ** 3, 4), np.float32)
+        pos4[:, :3] = (g + 0.5) * (box / m) + rng.uniform(-0.06, 0.06, (m ** 3, 3))
+        vel4 = np.zeros_like(pos4)
+        vel4[:, :3] = sign * 0.9 * 0.5 * (side - 2.5) / dt / np.sqrt(3.0)
+        path = [orc.run(p, pos4, vel4, k)[:2] for k in (1, 2, 3)]
+        if all(_clear_of_cutoff(x, box) for x, _ in path) and _clear_of_cutoff(pos4[:, :3].astype(np.float64), box):
+            break
+    _say(f"outside cells nc={nc} side={side} sign={sign} n={len(pos4)}")
+    s = _system(len(pos4), box, dt=dt, cell_min=0.999 * side, shift_mode=1)
+    assert s.cells_per_dim == nc
+    s.load(_dev(pos4), _dev(vel4))
+    s.step_every(3, 3)
+    _, vel = s.state()
+    assert s.check() == 0
+    assert np.abs(vel.cpu().numpy()[:, :3] - path[2][1]).max() < 3e-5
