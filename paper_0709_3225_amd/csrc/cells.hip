@@ -2,8 +2,10 @@
 // side >= r_c; section 3.1 membership kept current as particles move), and the
 // velocity-Verlet drift that feeds it (section 2).
 //
-// A build is two or three launches, four when a state is loaded on a small
-// grid:
+// A build on a grid of at most kDirectBlocks blocks of cells is two launches (bin,
+// cell order), or three when a state is loaded (bin, block count, cell order); on
+// larger grids it is four (bin, the scan's two, cell order). A load clears the
+// counters first, one launch more.
 //   bin        : wrap + cell index + histogram rank (one atomic per run of
 //                equal cells in a wavefront); the atom's position and
 //                velocity go to its cell's bucket (or the overflow list
