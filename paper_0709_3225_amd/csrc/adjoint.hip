@@ -191,7 +191,7 @@ __global__ void __launch_bounds__(MW * kWave)
             const int tn = min(a.tile_cap, total - t0);
             if (!rows) {
                 __syncthreads();
-                if (wv == 0) stage_tile<false, ADJ>(a, nb, tile, t0, tn, wvec, wtile);
+                if (wv == 0) stage_tile<ADJ>(a, nb, tile, t0, tn, wvec, wtile);
             }
             if (wv == 0) {
                 for (int t = lane; t < kTilePad; t += kWave) {
@@ -202,9 +202,9 @@ __global__ void __launch_bounds__(MW * kWave)
             __syncthreads();
             const int self_t = home_pos + h0 + h - t0;
             const uint32_t pad = lds_address(tile + tn);
-            for_each_words<false, kLongWords, false>(a, tile, tn, hl, nh, xi, yi, zi, a.screen2, a.screen16, self_t, wv, nw,
-                           [](auto&, int) { return false; },
-                           [&](auto& wd, int first, int, bool) {
+            for_each_words<false, kLongWords, false>(a, tile, tn, hl, nh, xi, yi, zi, a.screen2, a.screen16, self_t, wv,
+                                                     nw, [](auto&, int) { return false; },
+                                                     [&](auto& wd, int first, int) {
                 if constexpr (ADJ) {
                     AdjOp op{kc, 4 * lds_address(wtile) - 3 * lds_address(tile), xi, yi, zi, wi.x, wi.y, wi.z};
                     op.jx = v0; op.jy = v1; op.jz = v2; op.fx = v3; op.fy = v4; op.fz = v5; op.sg = v6;

@@ -188,9 +188,9 @@ __device__ __forceinline__ void load_neighbourhood(const SimArgs& a, int c, Neig
 // Staging of neighbourhood atoms [t0, t1) into the tile, frame-translated: a
 // uniform cursor (segment sg, neighbourhood index g) walks the segments in
 // chunks of at most one wavefront; a batch of B chunks has its loads in flight
-// before its LDS stores. w carries the user index (ID_IN_W) or |x|^2 in the
-// frame (for the screen); with WITH_VEC the matching entries of a per-atom
-// vector (sorted order) go to vtile as well.
+// before its LDS stores. w carries |x|^2 in the frame (for the screen); with
+// WITH_VEC the matching entries of a per-atom vector (sorted order) go to vtile
+// as well.
 struct StageCursor {
     int sg, g;
 };
@@ -257,7 +257,7 @@ __device__ __forceinline__ void stage_issue(const SimArgs& a, const HoodSegs& h,
 }
 
 // cur: the cursor stage_issue started from; on return, past the batch.
-template <int B, bool ID_IN_W, bool WITH_VEC, class VT>
+template <int B, bool WITH_VEC, class VT>
 __device__ __forceinline__ void stage_commit(const HoodSegs& h, const StageBatch<B, WITH_VEC>& b, StageCursor& cur,
                                              int t0, int t1, float4* tile, VT* vtile) {
     const int lane = __lane_id();
@@ -271,7 +271,7 @@ __device__ __forceinline__ void stage_commit(const HoodSegs& h, const StageBatch
                 const float x = b.q[u].x - lane_value(h.x, seg);
                 const float y = b.q[u].y - lane_value(h.y, seg);
                 const float z = b.q[u].z - lane_value(h.z, seg);
-                tile[dst] = make_float4(x, y, z, ID_IN_W ? b.q[u].w : x * x + y * y + z * z);
+                tile[dst] = make_float4(x, y, z, x * x + y * y + z * z);
                 if (WITH_VEC) put(vtile[dst], b.vq[u]);
             }
         }
@@ -288,7 +288,6 @@ __device__ __forceinline__ void stage_commit(const HoodSegs& h, const StageBatch
 // Atoms 64 and up of a longer segment follow, masked, after every segment's
 // first 64: no surplus store reaches that far (pos_j + 63 < pos_k + 64 for
 // j < k). The tile needs room for total + 63 entries.
-template <bool ID_IN_W>
 __device__ __forceinline__ void stage_whole(const SimArgs& a, const HoodSegs& h, float4* tile) {
     const int lane = __lane_id();
     const int nseg = h.nseg();  // 9 or 27
@@ -308,7 +307,7 @@ __device__ __forceinline__ void stage_whole(const SimArgs& a, const HoodSegs& h,
             const float x = q[u].x - lane_value(h.x, k);
             const float y = q[u].y - lane_value(h.y, k);
             const float z = q[u].z - lane_value(h.z, k);
-            tile[lane_value(h.pos, k) + lane] = make_float4(x, y, z, ID_IN_W ? q[u].w : x * x + y * y + z * z);
+            tile[lane_value(h.pos, k) + lane] = make_float4(x, y, z, x * x + y * y + z * z);
             // store as each load arrives: nine results held for one burst of
             // stores would cost 36 more registers
             __builtin_amdgcn_sched_barrier(0);
@@ -324,7 +323,7 @@ __device__ __forceinline__ void stage_whole(const SimArgs& a, const HoodSegs& h,
             if (off < len) {
                 const float4 q = a.pos0[first + off];
                 const float x = q.x - sx, y = q.y - sy, z = q.z - sz;
-                tile[pos + off] = make_float4(x, y, z, ID_IN_W ? q.w : x * x + y * y + z * z);
+                tile[pos + off] = make_float4(x, y, z, x * x + y * y + z * z);
             }
         }
     }
@@ -559,14 +558,14 @@ __device__ __forceinline__ void stage_hood(const SimArgs& a, const RowHood& r, f
 // 70.4 us with three, 69.1 with five, N = 32,000 and tiles of 192 atoms) and 3
 // for one of 12 bytes (the adjoint pass, whose registers are short: a seed at N =
 // 100,003 and tiles of 192 atoms 224 us with three, 229 with five).
-template <bool ID_IN_W, bool WITH_VEC = false, class VT = float4,
+template <bool WITH_VEC = false, class VT = float4,
           int B = (!WITH_VEC ? 9 : std::is_same_v<VT, float4> ? 5 : 3)>
 __device__ __forceinline__ void stage_tile(const SimArgs& a, const Neighbourhood& nb, float4* tile,
                                            int t0, int tn, const float4* vec = nullptr,
                                            VT* vtile = nullptr) {
     const HoodSegs h = hood_from_lds(nb);
     if (!WITH_VEC && t0 == 0 && tn == h.total()) {
-        stage_whole<ID_IN_W>(a, h, tile);
+        stage_whole(a, h, tile);
         return;
     }
     const int t1 = t0 + tn;
@@ -575,7 +574,7 @@ __device__ __forceinline__ void stage_tile(const SimArgs& a, const Neighbourhood
         StageBatch<B, WITH_VEC> b;
         StageCursor issue = cur;
         stage_issue(a, h, issue, t1, b, vec);
-        stage_commit<B, ID_IN_W>(h, b, cur, t0, t1, tile, vtile);
+        stage_commit<B>(h, b, cur, t0, t1, tile, vtile);
     }
 }
 
@@ -1107,11 +1106,11 @@ __device__ __forceinline__ void for_each_words(const SimArgs& a, const float4* t
                     }
                 }
                 const int first = g0 * NS + (hl.act ? hl.s : 0);
-                fn(wd, first, n1, had);
+                fn(wd, first, n1);
                 if (NS == 2 && groups > n1) {
                     if (!had) keep_first(groups - n1, wd2);  // likewise
-                    const bool had2 = kept(wd2, groups - n1);
-                    fn(wd2, first + 4 * nblk * NS, groups - n1, had2);
+                    kept(wd2, groups - n1);
+                    fn(wd2, first + 4 * nblk * NS, groups - n1);
                 }
             }
         };
@@ -1153,7 +1152,7 @@ __device__ __forceinline__ void for_each_words(const SimArgs& a, const float4* t
                 clear_self(g, g * ns == c, wd);
             }
         }
-        fn(wd, first, groups, had);
+        fn(wd, first, groups);
     }
 }
 

@@ -145,8 +145,9 @@ __device__ __forceinline__ void keep_words(uint4* rows, int& n, int groups, cons
 }
 
 // The kept words from record j on; record 0 and the two words of record 1 that
-// a walk of six takes were requested before the staging (w0, w1). Bits past the set's groups candidates per lane are dropped,
-// so a walk never leaves the staged span, whatever the words hold.
+// a walk of six takes were requested before the staging (w0, w1). Bits past the
+// set's groups candidates per lane are dropped, so a walk never leaves the staged
+// span, whatever the words hold.
 template <int WORDS>
 __device__ __forceinline__ void kept_words(const uint4* rows, const uint4& w0, const uint2& w1, int& j, int groups,
                                            uint32_t (&wd)[WORDS]) {
@@ -268,8 +269,8 @@ __device__ __forceinline__ void force_cell(const SimArgs& a, int c, float4* tile
             if (!rows) {
                 __syncthreads();
                 if (wv == 0) {
-                    if (EXPORT) stage_tile<false, true>(a, nb, tile, t0, tn, a.pos0, raw);
-                    else stage_tile<false>(a, nb, tile, t0, tn);
+                    if (EXPORT) stage_tile<true>(a, nb, tile, t0, tn, a.pos0, raw);
+                    else stage_tile(a, nb, tile, t0, tn);
                     if (LIST == 3) stage_codes(a, nb, reinterpret_cast<uint32_t*>(raw), t0, tn);
                 }
             }
@@ -287,8 +288,9 @@ __device__ __forceinline__ void force_cell(const SimArgs& a, int c, float4* tile
                 return false;
             };
             constexpr bool kKept = LIST == 1 || LIST == 2;
-            for_each_words<LIST == 3, kKept ? kKeptWords : kLongWords, kKept>(a, tile, tn, hl, nh, xi, yi, zi, bound, bound16, self_t, wv, nw, kept,
-                           [&](auto& wd, int first, int groups, bool) {
+            constexpr int kLong = kKept ? kKeptWords : kLongWords;
+            for_each_words<LIST == 3, kLong, kKept>(a, tile, tn, hl, nh, xi, yi, zi, bound, bound16, self_t, wv, nw,
+                                                    kept, [&](auto& wd, int first, int groups) {
                 if constexpr (LIST == 1) {
                     if (list_fits) keep_words(lwords, n_rec, groups, wd);
                 }

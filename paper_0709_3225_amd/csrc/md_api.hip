@@ -194,7 +194,8 @@ int waves_per_cell(const md_params* p) { return p->waves_per_cell != 0 ? p->wave
 // ceil(2^32 / nc): the kernels divide cell indices by nc through it (unused
 // for a batch's shared arguments, whose nc marks the batch).
 uint32_t division_magic(int nc) {
-    return nc < 2 ? 0u : static_cast<uint32_t>(((uint64_t{1} << 32) + static_cast<uint64_t>(nc) - 1) / static_cast<uint64_t>(nc));
+    const uint64_t d = static_cast<uint64_t>(nc);
+    return nc < 2 ? 0u : static_cast<uint32_t>(((uint64_t{1} << 32) + d - 1) / d);
 }
 
 SimArgs make_args(const md_params* p, const Layout& L, void* ws) {
